@@ -52,103 +52,199 @@ __device__ __forceinline__ void read_probs(const float* src, float (&e)[GP]) {
     }
 }
 
-// Several chunks per slab: a combine kernel after the chunks' launch, combine_parts(n) workgroups per slab:
-//   o_h = sum_c exp(m_c - M_h) o_c / sum_c exp(m_c - M_h) S_c,  M_h = max_c m_c   (part 0);
-//   r(row) = sum_{h in group} exp(z_h(row) - M_h) / S_h = sum_h e_h(row) exp(m_c - M_h) / S_h from the
-//   exponentials e_h = exp(z_h - m_c) the chunks wrote (c: the row's chunk), when emitting (part p: rows
-//   [p kCombineRows, (p + 1) kCombineRows)).
-// The rows are spread over several workgroups because one per slab left the score's rows (52 KB of logits per
-// slab at the 8B shape) to 64 workgroups at one decoder layer's batch.
+// Several chunks per slab: a combine kernel after the chunks' launch, combine_parts() workgroups per slab.  With
+//   f_h(c) = exp(m_c - M_h) / S_h,  M_h = max_c m_c,  S_h = sum_c exp(m_c - M_h) S_c
+// workgroup 0 of a slab adds the outputs, o_h = sum_c f_h(c) o_c, and, when emitting, workgroup 1 + p the scores of
+// rows [p kCombineRows, (p + 1) kCombineRows), r(row) = sum_{h in group} f_h(c) e_h(row) from the exponentials
+// e_h = exp(z_h - m_c) that the chunks wrote (c: the row's chunk).
+// The kernel moves little and is bound by its chain of memory latencies, so every thread issues all of its loads
+// (partial outputs of up to kAhead chunks, or the GP exponentials of its four rows) before the statistics are
+// taken, those come from one load per (head, chunk) staged in LDS, and outputs and rows are separate workgroups.
+// It had taken the chunks' pairs, then the outputs and the heads' rows in turn, one latency each.
 // Electing the last chunk of a slab inside the attention kernel instead was measured twice at the 8B shape:
 // with a device-scope release/acquire fence in every chunk (a full L2 write-back and invalidate) 5x slower per
 // layer; with the partials written and read back by device-scope (write-through) accesses and a completion
 // wait before the arrival count, no faster without the score (the chunk's store, count and reload round trips
 // cost what the kernel boundary does) and 9% slower with it (one workgroup per slab takes the score's rows).
-constexpr int kCombineRows = 1024;
-__host__ __device__ constexpr int combine_parts(int n, bool emit) { return emit ? (n + kCombineRows - 1) / kCombineRows : 1; }
+constexpr int kCombineThreads = 512;
+constexpr int kCombineRows = kCombineThreads * 4;
+constexpr int kCombineStaged = 1024;  // (head, chunk) pairs staged in LDS; more are taken from memory where needed
+__host__ __device__ constexpr int combine_parts(int n, bool emit) {
+    return 1 + (emit ? (n + kCombineRows - 1) / kCombineRows : 0);
+}
 
 template <typename T, int D, int GP>
-__global__ __launch_bounds__(kThreads) void attend_combine_kernel(ScoreArgs a) {
-    __shared__ float cm[GP], ci[GP];
+__global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(ScoreArgs a) {
+    constexpr int kAhead = 8;
+    __shared__ float2 pairs[kCombineStaged];
+    __shared__ float fs[kCombineStaged];
+    __shared__ float cm[GP], ci[GP];  // more chunks than are staged: M_h and 1 / S_h
     const int parts = combine_parts(a.n, a.emit);
     const int s = blockIdx.x / parts;  // slab: (l * batch + b) * hkv + g, l relative to the call
     const int part = blockIdx.x % parts;
-    const size_t head0 = (size_t)(s / a.hkv) * a.hq + (size_t)(s % a.hkv) * a.group;
-    // The loops over chunks load four chunks' values before using them (the loads are independent; the
-    // arithmetic keeps the sequential order, so the result does not depend on the unrolling).
-    constexpr int kU = 4;
-    if (threadIdx.x < a.group) {
-        const float2* pp = a.part + (head0 + threadIdx.x) * a.nchunk;
-        float mx = -INFINITY;
-        int c = 0;
-        for (; c + kU <= a.nchunk; c += kU) {
-            float2 p[kU];
+    const int tid = threadIdx.x, nchunk = a.nchunk, group = a.group;
+    const size_t head0 = (size_t)(s / a.hkv) * a.hq + (size_t)(s % a.hkv) * group;
+    const float2* pp = a.part + head0 * nchunk;  // [head][chunk]
+    const int npairs = group * nchunk;
+    const bool staged = npairs <= kCombineStaged;
+
+    // this thread's loads: four outputs of one head over the first chunks, or four rows of every head
+    constexpr int kQuads = D / 4;
+    const int h0 = tid / kQuads, d0 = tid % kQuads * 4;
+    auto out_of = [&](int h, int c) __attribute__((always_inline)) {
+        return *reinterpret_cast<const f32x4*>(a.opart + ((head0 + h) * nchunk + c) * D + d0);
+    };
+    const int row = (part - 1) * kCombineRows + tid * 4;  // rows >= n up to the padded stride are scratch
+    f32x4 x[GP > kAhead ? GP : kAhead];
+    if (part == 0) {
 #pragma unroll
-            for (int j = 0; j < kU; ++j) p[j] = pp[c + j];
+        for (int c = 0; c < kAhead; ++c)
+            if (h0 < group && c < nchunk) x[c] = out_of(h0, c);
+    } else if (row < a.n) {
 #pragma unroll
-            for (int j = 0; j < kU; ++j) mx = fmaxf(mx, p[j].x);
-        }
-        for (; c < a.nchunk; ++c) mx = fmaxf(mx, pp[c].x);
-        float tot = 0.0f;
-        for (c = 0; c + kU <= a.nchunk; c += kU) {
-            float2 p[kU];
-#pragma unroll
-            for (int j = 0; j < kU; ++j) p[j] = pp[c + j];
-#pragma unroll
-            for (int j = 0; j < kU; ++j) tot = fmaf(__expf(p[j].x - mx), p[j].y, tot);
-        }
-        for (; c < a.nchunk; ++c) tot = fmaf(__expf(pp[c].x - mx), pp[c].y, tot);
-        cm[threadIdx.x] = mx;
-        ci[threadIdx.x] = tot > 0.0f ? 1.0f / tot : 0.0f;
+        for (int h = 0; h < GP; ++h)
+            if (h < group) x[h] = *reinterpret_cast<const f32x4*>(a.z + (head0 + h) * a.n_stride + row);
     }
-    if (a.emit_norms && part == 0 && threadIdx.x == kWave) {  // (another wave than the one filling cm / ci)
-        float tot = 0.0f;
-        for (int c = 0; c < a.nchunk; ++c) tot += a.npart[(size_t)s * a.nchunk + c];
-        a.vinv[s] = tot > 0.0f ? (float)a.n / tot : 0.0f;
+
+    if (staged) {
+        for (int i = tid; i < npairs; i += kCombineThreads) pairs[i] = pp[i];
+        __syncthreads();
+        for (int i = tid; i < npairs; i += kCombineThreads) {
+            const float2* ph = pairs + i / nchunk * nchunk;
+            float mx = ph[0].x;
+            for (int c = 1; c < nchunk; ++c) mx = fmaxf(mx, ph[c].x);
+            float tot = 0.0f;
+            for (int c = 0; c < nchunk; ++c) tot = fmaf(__expf(ph[c].x - mx), ph[c].y, tot);
+            fs[i] = tot > 0.0f ? __expf(pairs[i].x - mx) / tot : 0.0f;
+        }
+    } else if (tid < group) {
+        const float2* ph = pp + (size_t)tid * nchunk;
+        float mx = -INFINITY, tot = 0.0f;
+        for (int c = 0; c < nchunk; ++c) mx = fmaxf(mx, ph[c].x);
+        for (int c = 0; c < nchunk; ++c) tot = fmaf(__expf(ph[c].x - mx), ph[c].y, tot);
+        cm[tid] = mx;
+        ci[tid] = tot > 0.0f ? 1.0f / tot : 0.0f;
     }
     __syncthreads();
-    T* ob = static_cast<T*>(a.o) + head0 * D;
-    for (int idx = threadIdx.x; part == 0 && idx < a.group * D; idx += kThreads) {
-        const int h = idx / D;
-        const float2* pp = a.part + (head0 + h) * a.nchunk;
-        const float* op = a.opart + (head0 + h) * a.nchunk * D + idx % D;
-        float acc = 0.0f;
-        int c = 0;
-        for (; c + kU <= a.nchunk; c += kU) {
-            float m[kU], x[kU];
+    auto factor = [&](int h, int c) __attribute__((always_inline)) {
+        return staged ? fs[h * nchunk + c] : __expf(pp[(size_t)h * nchunk + c].x - cm[h]) * ci[h];
+    };
+
+    if (part != 0) {
+        if (row >= a.n) return;
+        const int c = row / a.chunk_rows;  // four rows lie in one chunk: chunks are a multiple of 4 rows
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int j = 0; j < kU; ++j) {
-                m[j] = pp[c + j].x;
-                x[j] = op[(size_t)(c + j) * D];
-            }
-#pragma unroll
-            for (int j = 0; j < kU; ++j) acc = fmaf(__expf(m[j] - cm[h]), x[j], acc);
-        }
-        for (; c < a.nchunk; ++c) acc = fmaf(__expf(pp[c].x - cm[h]), op[(size_t)c * D], acc);
-        Elem<T>::store(ob + idx, acc * ci[h]);
+        for (int h = 0; h < GP; ++h)
+            if (h < group) acc += x[h] * factor(h, c);
+        *reinterpret_cast<f32x4*>(a.r + (size_t)s * a.n_stride + row) = acc;
+        return;
     }
-    if (a.emit) {
-        // the rows hold e_h(row) = exp(z - m_c) of their chunk c (4 rows per thread and pass lie in one chunk: chunks
-        // are a multiple of 4 rows; rows are padded to a multiple of 64, rows >= n are scratch):
-        // r(row) = sum_h e_h(row) exp(m_c - M_h) / S_h
-        const float* zb = a.z + head0 * a.n_stride;
-        float* rb = a.r + (size_t)s * a.n_stride;
-        const int row_end = min(a.n, (part + 1) * kCombineRows);
-        for (int row = part * kCombineRows + threadIdx.x * 4; row < row_end; row += kThreads * 4) {
-            const int c = row / a.chunk_rows;
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int h = 0; h < a.group; ++h) {
-                const f32x4 e = *reinterpret_cast<const f32x4*>(zb + (size_t)h * a.n_stride + row);
-                const float f = __expf(a.part[(head0 + h) * a.nchunk + c].x - cm[h]) * ci[h];
-                acc.x += e.x * f;
-                acc.y += e.y * f;
-                acc.z += e.z * f;
-                acc.w += e.w * f;
-            }
-            *reinterpret_cast<f32x4*>(rb + row) = acc;
+    if (a.emit_norms && tid / kWave == kCombineThreads / kWave - 1) {
+        float tot = 0.0f;
+        for (int c = tid % kWave; c < nchunk; c += kWave) tot += a.npart[(size_t)s * nchunk + c];
+        tot = wave_sum(tot);
+        if (tid % kWave == 0) a.vinv[s] = tot > 0.0f ? (float)a.n / tot : 0.0f;
+    }
+    T* ob = static_cast<T*>(a.o) + head0 * D;
+    for (int h = h0; h < group; h += kCombineThreads / kQuads) {
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int c0 = 0; c0 < nchunk; c0 += kAhead) {
+            if (h != h0 || c0 != 0)
+#pragma unroll
+                for (int c = 0; c < kAhead; ++c)
+                    if (c0 + c < nchunk) x[c] = out_of(h, c0 + c);
+#pragma unroll
+            for (int c = 0; c < kAhead; ++c)
+                if (c0 + c < nchunk) acc += x[c] * factor(h, c0 + c);
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Elem<T>::store(ob + h * D + d0 + j, acc[j]);
     }
 }
+
+// Matrix-core V pass, for bf16 rows of d = 128 and padded groups of 4 to 16: the product of the group's
+// probabilities with the rows' values, 16 rows at a time, as v_mfma_f32_16x16x16_bf16 with the rows as the
+// contracted index.
+//  * V: load j of a unit gives lane 16 g + p the 16 bytes p (columns 8 p .. 8 p + 7) of row 4 j + g, so one load
+//    instruction reads 1 KiB of consecutive rows.  Element j of the contraction's slice g is taken to be row 4 j + g;
+//    a column of the lane's four rows then needs only byte permutes of the lane's own registers, and MFMA x covers
+//    the columns 8 p + x (p < 16), eight of them the whole row.
+//  * probabilities: lane 16 g + h holds those of head h for the same rows.  They stay 32-bit numbers: each is the
+//    sum of three bf16 parts (its upper 8 significant bits, the next 8, the last 8: exact), and each part takes an
+//    MFMA of its own, whose products are exact and accumulated in fp32.
+//  * the result of MFMA x in lane 16 g + p is heads 4 g .. 4 g + 3 of column 8 p + x: nothing is left to be added
+//    across lanes.
+// On the vector ALUs each lane held GP x 16 accumulators (8 heads), which a wave then added across its lanes with
+// LDS-crossbar shuffles and the workgroup wave by wave: 64 us for one layer of 32 sequences x 4 KV heads x 2,049 rows
+// (7 heads per KV head), 25 us so; with 4 heads (8 sequences x 8 KV heads x 3,278 rows) 0.3 us of 25 per layer
+// call.  Units of 32 rows (16x16x32 MFMAs, two units in flight) left the waves further apart at the end of the
+// pass: 882 against 871 us for 28 layer calls of the former shape; three or four units of 16 rows in flight 877 and
+// 901.  Groups of 1 and 2 keep the vector form: its accumulators are few and most of an MFMA would be padding.
+typedef short __attribute__((ext_vector_type(4))) s16x4;
+typedef uint32_t __attribute__((ext_vector_type(2))) u32x2;
+
+template <typename T, int D, int GP>
+constexpr bool use_mfma_v() {
+    return std::is_same<T, bf16_t>::value && D == 128 && GP >= 4;
+}
+
+struct VUnit {
+    static constexpr int kRows = 16;
+    static constexpr int kN = kRows / 4;  // rows per lane
+    static constexpr int kRowBytes = 256;
+    typedef u32x4 buf_t[kN];
+    int g, p;
+    __device__ VUnit() {
+        const int lane = threadIdx.x & (kWave - 1);
+        g = lane / 16;
+        p = lane % 16;
+    }
+    __device__ int row(int u, int j) const { return u * kRows + 4 * j + g; }
+    // LDS word of (row 4 j + g of the unit, head 0) from the unit's first: see KUnit for the layout of the blocks
+    template <int GP>
+    __device__ static int word(int g, int j) {
+        return GP >= 8 ? (4 * j + g) * GP : j / 4 * kWave + g * 16 + j % 4 * 4;
+    }
+    __device__ void load(__amdgpu_buffer_rsrc_t vrs, int u, buf_t& dst) const {
+        const int off = (u * kRows + g) * kRowBytes + p * 16;
+#pragma unroll
+        for (int j = 0; j < kN; ++j)
+            dst[j] = __builtin_amdgcn_raw_buffer_load_b128(vrs, off + j * 4 * kRowBytes, 0,
+                                                           IKV_NT_LOADS ? kNonTemporal : 0);
+    }
+    // halves of two registers as one: the low ones (even columns) or the high ones (odd columns, or the upper 16
+    // bits of two floats)
+    __device__ static uint32_t low2(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+    __device__ static uint32_t high2(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+    __device__ static f32x4 mfma(u32x2 a, u32x2 b, f32x4 acc) {
+        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b),
+                                                         acc, 0, 0, 0);
+    }
+    // acc[x] += probabilities e (rows row(u, 0 .. kN - 1) of head p; zero for heads and rows that are none) times V
+    __device__ static void add(const buf_t& v, float (&e)[kN], f32x4 (&acc)[8]) {
+        u32x2 part[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+#pragma unroll
+            for (int i = 0; i < kN / 2; ++i) part[k][i] = high2(__float_as_uint(e[2 * i]), __float_as_uint(e[2 * i + 1]));
+            if (k < 2)
+#pragma unroll
+                for (int j = 0; j < kN; ++j) e[j] -= __uint_as_float(__float_as_uint(e[j]) & 0xffff0000u);
+        }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            u32x2 c;
+#pragma unroll
+            for (int i = 0; i < kN / 2; ++i)
+                c[i] = x % 2 ? high2(v[2 * i][x / 2], v[2 * i + 1][x / 2]) : low2(v[2 * i][x / 2], v[2 * i + 1][x / 2]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                acc[x] = mfma(part[k], c, acc[x]);
+            }
+        }
+    }
+};
 
 // Waves per SIMD the compiler must leave room for: bf16 rows of d = 128 with groups of 4 (the 8B shape) are held
 // to 128 registers, i.e. two workgroups per CU, which the all-layer call (2,048 workgroups) uses: uncapped the
@@ -175,10 +271,12 @@ void attend_kernel(ScoreArgs a) {
 
     // the waves' partial outputs are added in one step when every wave's slice fits 16 KiB of LDS (GP * D <= 512
     // floats: groups up to 4 at d = 128), else wave by wave (one barrier each); the sums are the same
-    constexpr bool kWaveSlices = kWaves * GP * D <= 4096;
+    constexpr bool kMV = kV && use_mfma_v<T, D, GP>();
+    constexpr bool kWaveSlices = kWaves * GP * D <= 4096 && !kMV;
+    constexpr int kMVSlices = GP > 8 ? kWaves / 2 : kWaves;  // matrix-core form: at most 32 KiB of slices
     extern __shared__ float zs[];
     __shared__ float red_m[kWaves][GP], red_s[kWaves][GP], red_n[kWaves];
-    __shared__ float obuf[kV ? (kWaveSlices ? kWaves : 1) * GP * D : 1];
+    __shared__ float obuf[kV ? (kMV ? kMVSlices : kWaveSlices ? kWaves : 1) * GP * D : 1];
     __shared__ int next_unit[2];
 
     const L ln;
@@ -223,9 +321,20 @@ void attend_kernel(ScoreArgs a) {
 
     // the V stream's first loads are issued now, so their latency overlaps the K pass's epilogue (barriers
     // wait for LDS only, not for these loads)
-    chunk_t vbuf[kNbuf][RPG][CPL];
+    chunk_t vbuf[kMV ? 1 : kNbuf][RPG][CPL];
     int vfirst = -1;
-    if constexpr (kV && kNbuf == 2) {
+    const VUnit vu;
+    constexpr int kNbufV = 2;
+    int vnext[kNbufV];
+    typename VUnit::buf_t vbufm[kMV ? kNbufV : 1];
+    const int nvu = kMV ? (nrows + VUnit::kRows - 1) / VUnit::kRows : nunits;
+    if constexpr (kMV) {
+#pragma unroll
+        for (int j = 0; j < kNbufV - 1; ++j) {
+            vnext[j] = claim(1);
+            vu.load(vrs, vnext[j], vbufm[j]);
+        }
+    } else if constexpr (kV && kNbuf == 2) {
         vfirst = claim(1);
         ln.load_rows(vrs, vfirst, vbuf[0]);
     }
@@ -301,14 +410,77 @@ void attend_kernel(ScoreArgs a) {
     const __amdgpu_buffer_rsrc_t vns =
         raw_rsrc(a.vn + (size_t)s * a.n_stride + row0, a.emit_norms ? nrows * 4 : 0);
     float nsum = 0.0f;
-    float acc[GP][CPL][EPC];
+    f32x4 accm[kMV ? 8 : 1];
+    float acc[kMV ? 1 : GP][kMV ? 1 : CPL][EPC];
+    if constexpr (kMV) {
 #pragma unroll
-    for (int h = 0; h < GP; ++h)
+        for (int x = 0; x < 8; ++x) accm[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        const int h = vu.p;  // the head whose probabilities this lane supplies (none past GP)
+        float mh = 0.0f;
+        if (h < GP) {
+            mh = red_m[0][h];
 #pragma unroll
-        for (int c = 0; c < CPL; ++c)
+            for (int w = 1; w < kWaves; ++w) mh = fmaxf(mh, red_m[w][h]);
+        }
+        auto& ubuf = vnext;
+        bool more = true;
+        while (more) {
 #pragma unroll
-            for (int x = 0; x < EPC; ++x) acc[h][c][x] = 0.0f;
-    {
+            for (int j = 0; j < kNbufV; ++j) {
+                const int slot = (j + kNbufV - 1) % kNbufV;
+                ubuf[slot] = claim(1);
+                vu.load(vrs, ubuf[slot], vbufm[slot]);
+                if (more && ubuf[j] < nvu) {
+                    // all of the lane's words are read before any is used; rows past the chunk and padded lanes
+                    // read word 0 and count as zero
+                    float e[VUnit::kN];
+                    int word[VUnit::kN];
+                    bool in[VUnit::kN];
+#pragma unroll
+                    for (int r = 0; r < VUnit::kN; ++r) {
+                        in[r] = h < GP && vu.row(ubuf[j], r) < nrows;
+                        word[r] = in[r] ? ubuf[j] * VUnit::kRows * GP + VUnit::word<GP>(vu.g, r) + h : 0;
+                        e[r] = zs[word[r]];
+                    }
+                    if (!exp_apart) {
+#pragma unroll
+                        for (int r = 0; r < VUnit::kN; ++r) {
+                            e[r] = in[r] ? __expf(e[r] - mh) : 0.0f;
+                            ssum += e[r];
+                        }
+                        if (a.emit)
+#pragma unroll
+                            for (int r = 0; r < VUnit::kN; ++r)
+                                if (in[r]) zs[word[r]] = e[r];
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < VUnit::kN; ++r) e[r] = in[r] ? e[r] : 0.0f;
+                    }
+                    if (a.emit_norms) {  // VNorm: the rows' l2 norms, summed over the 16 lanes of a row
+#pragma unroll
+                        for (int r = 0; r < VUnit::kN; ++r) {
+                            const chunk_t c[1] = {vbufm[j][r]};
+                            const float nrm = row_norm_lanes<T, 16, 1>(c);
+                            const int row = vu.row(ubuf[j], r);
+                            if (vu.p == 0 && row < nrows) {
+                                store_stream(vns, row * 4, nrm);
+                                nsum += nrm;
+                            }
+                        }
+                    }
+                    VUnit::add(vbufm[j], e, accm);
+                } else {
+                    more = false;
+                }
+            }
+        }
+    } else {
+#pragma unroll
+        for (int h = 0; h < GP; ++h)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c)
+#pragma unroll
+                for (int x = 0; x < EPC; ++x) acc[h][c][x] = 0.0f;
         int ubuf[kNbuf];
         if constexpr (kNbuf == 2) ubuf[0] = vfirst;
         bool more = true;
@@ -367,8 +539,9 @@ void attend_kernel(ScoreArgs a) {
         if (ln.lane == 0) red_n[ln.wave] = nsum;  // read after the barriers below
     }
     if (!exp_apart) {  // the sums the waves took over the blocks they claimed
+        if constexpr (!kMV)
 #pragma unroll
-        for (int o = GP; o < 16; o <<= 1) ssum += __shfl_xor(ssum, o, kWave);
+            for (int o = GP; o < 16; o <<= 1) ssum += __shfl_xor(ssum, o, kWave);
         ssum = rows_allsum(ssum);
         if (ln.lane < GP) red_s[ln.wave][ln.lane] = ssum;  // read after the barriers below
     }
@@ -381,7 +554,7 @@ void attend_kernel(ScoreArgs a) {
     //    ~1 us after the V pass.
     constexpr int kAcc = GP * CPL * EPC;
     constexpr bool kRowSwaps = kWaveSlices && LPR == 16 && kAcc % 4 == 0;
-    if constexpr (!kRowSwaps) {
+    if constexpr (!kRowSwaps && !kMV) {
 #pragma unroll
         for (int o = LPR; o < kWave; o <<= 1)
 #pragma unroll
@@ -391,7 +564,52 @@ void attend_kernel(ScoreArgs a) {
 #pragma unroll
                     for (int x = 0; x < EPC; ++x) acc[h][c][x] += __shfl_xor(acc[h][c][x], o, kWave);
     }
-    if constexpr (kWaveSlices) {
+    if constexpr (kMV) {
+        // nothing to add across lanes: each wave's (or, for 16 heads, each pair of waves') partial in a slice of its
+        // own, then the slices in order by the thread that later stores the output
+        auto slice_of = [&](int i, int half) __attribute__((always_inline)) {
+            return reinterpret_cast<f32x4*>(obuf + ln.wave % kMVSlices * GP * D + (4 * vu.g + i) * D + 8 * vu.p) + half;
+        };
+        if (ln.wave < kMVSlices && 4 * vu.g < GP)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int half = 0; half < 2; ++half)
+                    *slice_of(i, half) = f32x4{accm[4 * half][i], accm[4 * half + 1][i], accm[4 * half + 2][i],
+                                               accm[4 * half + 3][i]};
+        __syncthreads();
+        if constexpr (kMVSlices < kWaves) {
+            if (ln.wave >= kMVSlices && 4 * vu.g < GP)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int half = 0; half < 2; ++half)
+                        *slice_of(i, half) += f32x4{accm[4 * half][i], accm[4 * half + 1][i], accm[4 * half + 2][i],
+                                                    accm[4 * half + 3][i]};
+            __syncthreads();
+        }
+        for (int idx = threadIdx.x; idx < a.group * D; idx += kThreads) {
+            float t = obuf[idx];
+#pragma unroll
+            for (int w = 1; w < kMVSlices; ++w) t += obuf[w * GP * D + idx];
+            // A value row with an infinity or NaN: the zero parts of a probability turn it into NaN here, where the
+            // product e v itself may be an infinity.  Taken again, product by product.
+            if (!(fabsf(t) < INFINITY)) {
+                const int h = idx / D;
+                float mh = red_m[0][h];
+                for (int w = 1; w < kWaves; ++w) mh = fmaxf(mh, red_m[w][h]);
+                const bool logits = !exp_apart && !a.emit;
+                t = 0.0f;
+                for (int row = 0; row < nrows; ++row) {
+                    const int rib = row % RPW;
+                    const float z = zs[row / RPW * kWave + rib % L::NG * LPR + rib / L::NG * GP + h];
+                    const uint32_t bits = static_cast<const bf16_t*>(a.v)[base + (size_t)row * D + idx % D].bits;
+                    t = fmaf(logits ? __expf(z - mh) : z, __uint_as_float(bits << 16), t);
+                }
+            }
+            obuf[idx] = t;
+        }
+    } else if constexpr (kWaveSlices) {
         // each wave's partial in its own slice; then output idx = ((w0 + w1) + w2) + ... by the thread that later
         // stores it (the same thread-to-output mapping as the stores below, so no barrier between)
         float* slice = obuf + ln.wave * GP * D;
@@ -442,8 +660,11 @@ void attend_kernel(ScoreArgs a) {
         // thread and 16-byte store; rows past the chunk give 0 (rows are padded to a multiple of 64)
         float* zc = a.z + ((size_t)lb * a.hq + (size_t)g * a.group) * a.n_stride + row0;
         const int quads = (nrows + 3) / 4;
-        for (int t = threadIdx.x; t < a.group * quads; t += kThreads) {
-            const int h = t / quads, r0 = t % quads * 4;
+        for (int t = threadIdx.x; t < GP * quads; t += kThreads) {
+            // heads vary fastest: a wave's LDS reads then spread over the banks (rows fastest, the 8-head layout's
+            // stride of 32 words between a wave's threads put them all on two)
+            const int h = t % GP, r0 = t / GP * 4;
+            if (h >= a.group) continue;
             f32x4 e;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -539,7 +760,8 @@ hipError_t launch_attend_gp(const ScorePlan& plan, const ScoreArgs& a, hipStream
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL((attend_combine_kernel<T, D, GP>),
-                               dim3(plan.grid / plan.nchunk * combine_parts(a.n, a.emit)), dim3(kThreads), 0, s, a);
+                               dim3(plan.grid / plan.nchunk * combine_parts(a.n, a.emit)), dim3(kCombineThreads),
+                               0, s, a);
         }
         return hipGetLastError();
     }

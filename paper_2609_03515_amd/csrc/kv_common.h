@@ -45,6 +45,14 @@ __device__ __forceinline__ float group_allsum(float x) {
     return x;
 }
 
+// Maximum over the lane's 16-lane row; every lane of the row gets it.
+__device__ __forceinline__ float row_allmax(float x) {
+    x = fmaxf(x, dpp<kXor1>(x));
+    x = fmaxf(x, dpp<kXor2>(x));
+    x = fmaxf(x, dpp<kMirror8>(x));
+    return fmaxf(x, dpp<kRor8>(x));
+}
+
 // Reduce-scatter of V = W values over an aligned group of W lanes: afterwards v[0] of the lane with in-group
 // index p holds the group total of value index p.  At each step the lane keeps the half of the remaining
 // indices selected by its own bit and adds the partner's copy of the same indices.

@@ -395,9 +395,7 @@ struct KUnit<T, D, GP, true> {
     }
     __device__ void publish_max(max_t m, float* red) const {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) m[i] = fmaxf(m[i], __shfl_xor(m[i], o, kWave));
+        for (int i = 0; i < 4; ++i) m[i] = row_allmax(m[i]);
         if (col == 0 && kq * 4 < GP)
 #pragma unroll
             for (int i = 0; i < 4; ++i) red[kq * 4 + i] = m[i];

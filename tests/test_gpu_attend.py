@@ -187,6 +187,57 @@ def test_attend_geometries(dtype, d, hq, hkv, n):
     assert_close(s_out.cpu().numpy(), s_ref, "scores from the attention")
 
 
+@pytest.mark.parametrize("group", [3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("n", [1, 15, 17, 255, 257, 1033])
+def test_attend_value_pass_edges(group, n):
+    """The value pass on the matrix cores (bf16, d = 128, padded groups of 4 to 16) at the edges of its 16-row
+    units and of the chunks, one chunk per slab and several, with rows whose scales differ by 2^20; then with an
+    infinity and a NaN among the values, which reach their own column of every head and no other.
+
+    Bound per output, relative to sum_i a(i) |v_i|: a logit is a sum of 128 products of fp32 rounding, at most
+    128 * 2^-24 of sum |q k| / sqrt(d) <= 16, and moves its probability by as much: 1.3e-4; the products and their
+    sum add n * 2^-24 <= 6.2e-5; together 2e-4, and 2^-8 of the output for its rounding to bf16."""
+    b, hkv, d = 2, 2, 128
+    hq = group * hkv
+    gen = torch.Generator(device="cpu").manual_seed(1000 * group + n)
+    cap = n + 5
+    k = torch.randn(1, b, hkv, cap, d, generator=gen).clamp_(-4, 4).to(torch.bfloat16)
+    v = torch.randn(1, b, hkv, cap, d, generator=gen)
+    v *= 2.0 ** torch.randint(-10, 11, (1, b, hkv, cap, 1), generator=gen)
+    v = v.to(torch.bfloat16)
+    q = (0.5 * torch.randn(1, b, hq, d, generator=gen)).clamp_(-2, 2).to(torch.bfloat16)
+    pos = torch.arange(cap, dtype=torch.int32).repeat(b, 1).contiguous()
+    shape = B.make_shape(b, 1, hq, hkv, d, cap, "bf16")
+    ws = B.workspace(shape, n)
+    dk, dq, dpos = k.cuda(), q.cuda(), pos.cuda()
+
+    def attend(values):
+        o = torch.empty_like(dq)
+        B.kv_attend_score(shape, 0, 1, n, dq, dk, values.cuda(), dpos, n - 1, 0.0, 0, B.KV_EMIT_SCORES, o, ws)
+        torch.cuda.synchronize()
+        return to_f64(raw_numpy(o), "bf16")
+
+    print(f"value pass group={group} n={n}", flush=True)
+    kr, vr, qr = raw_numpy(k), raw_numpy(v), raw_numpy(q)
+    ref, scale = np.zeros((1, b, hq, d)), np.zeros((1, b, hq, d))
+    for bb in range(b):
+        ref[0, bb], scale[0, bb] = attention_output(to_f64(qr[0, bb], "bf16"), to_f64(kr[0, bb, :, :n], "bf16"),
+                                                    to_f64(vr[0, bb, :, :n], "bf16"), pos.numpy()[bb, :n].astype(np.int64),
+                                                    n - 1, 0.0, 0)
+    got = attend(v)
+    assert np.all(np.abs(got - ref) <= 2e-4 * scale + 2.0 ** -8 * np.abs(ref))
+    odd = v.clone()
+    odd[0, 0, 1, n // 2, 7] = float("inf")
+    odd[0, 1, 0, n - 1, 100] = float("nan")
+    odd[0, 1, 0, 0, 9] = float("-inf")
+    got2 = attend(odd)
+    assert np.all(np.isposinf(got2[0, 0, group:, 7])) and np.all(np.isnan(got2[0, 1, :group, 100]))
+    assert np.all(np.isneginf(got2[0, 1, :group, 9]))
+    same = np.ones_like(got, dtype=bool)
+    same[0, 0, group:, 7] = same[0, 1, :group, 100] = same[0, 1, :group, 9] = False
+    assert np.all(np.abs(got2 - got)[same] <= (4e-4 * scale + 2.0 ** -7 * np.abs(ref))[same])
+
+
 @pytest.mark.parametrize("merge,entropy", [(0, False), (1, False), (2, False), (4, False), (8, False), (4, True)],
                          ids=["auto", "merge1", "merge2", "merge4", "merge8", "merge4_entropy"])
 def test_fused_scores_equal_separate_pass_bitwise(merge, entropy):
