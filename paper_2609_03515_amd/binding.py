@@ -124,6 +124,10 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
+        # the current device's current stream.  Building torch's Stream object for it took 2.9 us of a call's 13
+        # (one eviction step) or 10 (one layer's attention); the raw handle takes 0.2
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
