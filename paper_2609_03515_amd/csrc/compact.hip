@@ -128,23 +128,31 @@ __global__ __launch_bounds__(kThreads) void append_kernel(AppendArgs a) {
     reinterpret_cast<u32x4*>(dst)[c] = reinterpret_cast<const u32x4*>(src)[c];
 }
 
-// Decision of a non-refresh step of one sequence whose cache holds n_in <= B tokens (every Lazy / Score-Free
-// step after the first), in one pass over u and pos: the newcomer's prior (mean or min of the n_in utilities,
-// as append_kernel) and the minimum of the cached tokens under (u ascending, position descending); the
-// newcomer is then compared with that minimum (select_kernel's one-eviction rule over the n_in + 1 tokens).
-// The newcomer takes the evicted slot (the same cache, u and pos as append + select + hole-fill), slot n_in
-// when nothing is evicted, or no slot when it is itself evicted (slot[b] = -1); its rows are copied here
-// (copy_rows) or by newcomer_rows_kernel.
+// A non-refresh step of one sequence whose cache holds n_in <= B tokens (every Lazy / Score-Free step after the
+// first), in one pass over u and pos: the newcomer's prior (mean or min of the n_in utilities, as append_kernel) and
+// the minimum of the cached tokens under (u ascending, position descending); the newcomer is then compared with
+// that minimum (select_kernel's one-eviction rule over the n_in + 1 tokens).  The newcomer takes the evicted slot
+// (the same cache, u and pos as append + select + hole-fill), slot n_in when nothing is evicted, or no slot when it
+// is itself evicted (slot[b] = -1).
+// Its rows, per kRows: kRowsApart: copied by newcomer_rows_kernel; kRowsAfter: here, once the slot is known;
+// kRowsAhead: here, loaded while the decision's own loads are in flight, so that after it only the stores are left
+// (at most kAheadBytes, kCopy chunks per thread).
+// The kernel is one chain of latencies (arguments, u and pos, the reductions, the stores): all of a thread's u and
+// pos are in flight together up to 16,384 tokens, and the last reduction is a wave's instead of one thread's: back
+// to back 6.1 -> 4.7 us for 8 sequences of 3,277 tokens (lowest prior), 7.4 -> 6.2 us for 2 of 13,107.
 constexpr int kNrThreads = 1024;
 constexpr int kNrWaves = kNrThreads / kWave;
+constexpr int kCopy = 4;
+constexpr long long kAheadBytes = (long long)kNrThreads * kCopy * 16;
+enum { kRowsApart = 0, kRowsAfter = 1, kRowsAhead = 2 };
 
 using Cand = EvictCand;
 
+template <int kRows, int kBatch>
 __global__ __launch_bounds__(kNrThreads) void nonrefresh_kernel(AppendArgs a, uint8_t* keep_out, int budget,
-                                                                int* slot_out, int copy_rows) {
+                                                                int* slot_out) {
     __shared__ float red[kNrWaves];
     __shared__ Cand best[kNrWaves];
-    __shared__ int slot_sh;
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     float* ub = a.u + (size_t)b * a.cap;
@@ -152,23 +160,65 @@ __global__ __launch_bounds__(kNrThreads) void nonrefresh_kernel(AppendArgs a, ui
     const int n = a.n_in;
     const bool use_min = a.init_mode == 2;
 
+    // 16-byte chunk c of the newcomer's rows r = (tensor, l, g) in [0, 2 L hkv); quotients by float reciprocals
+    // (exact: the numerators are far below 2^22 and the +0.5 keeps them off integer boundaries)
+    const int lpr = a.row_bytes / 16;
+    const int total = a.layers * a.hkv * 2 * lpr;
+    const float inv_lpr = 1.0f / (float)lpr, inv_hkv = 1.0f / (float)a.hkv, inv_lg = 1.0f / (float)(a.layers * a.hkv);
+    auto chunk_of = [&](int c, bool& isv, int& ch) __attribute__((always_inline)) {
+        const int r = (int)(((float)c + 0.5f) * inv_lpr);
+        ch = c - r * lpr;
+        const int tensor = (int)(((float)r + 0.5f) * inv_lg);
+        const int lg = r - tensor * a.layers * a.hkv;
+        const int l = (int)(((float)lg + 0.5f) * inv_hkv);
+        isv = tensor != 0;
+        return ((size_t)l * a.batch + b) * a.hkv + (lg - l * a.hkv);
+    };
+    u32x4 buf[kCopy];
+    auto load_rows = [&](int c0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kCopy; ++j) {
+            const int c = c0 + j * kNrThreads;
+            if (c < total) {
+                bool isv;
+                int ch;
+                const size_t row = chunk_of(c, isv, ch);
+                buf[j] = reinterpret_cast<const u32x4*>(static_cast<const char*>(isv ? a.v_new : a.k_new) +
+                                                        row * a.row_bytes)[ch];
+            }
+        }
+    };
+    auto store_rows = [&](int c0, int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kCopy; ++j) {
+            const int c = c0 + j * kNrThreads;
+            if (c < total) {
+                bool isv;
+                int ch;
+                const size_t row = chunk_of(c, isv, ch);
+                reinterpret_cast<u32x4*>(static_cast<char*>(isv ? a.v : a.k) + (row * a.cap + slot) * a.row_bytes)[ch] =
+                    buf[j];
+            }
+        }
+    };
+
     float v = use_min ? INFINITY : 0.0f;
     Cand c{0xffffffffu, -1, -1};
-    // kNrBatch tokens' loads in flight per thread; the reduction keeps the order of a plain sweep
-    constexpr int kNrBatch = 8;
-    for (int i0 = tid; i0 < n; i0 += kNrThreads * kNrBatch) {
-        float uu[kNrBatch];
-        int pp[kNrBatch];
+    // kBatch tokens' loads in flight per thread; the reduction keeps the order of a plain sweep
+    for (int i0 = tid; i0 < n; i0 += kNrThreads * kBatch) {
+        float uu[kBatch];
+        int pp[kBatch];
 #pragma unroll
-        for (int j = 0; j < kNrBatch; ++j) {
+        for (int j = 0; j < kBatch; ++j) {
             const int i = i0 + j * kNrThreads;
             if (i < n) {
                 uu[j] = ub[i];
                 pp[j] = pb[i];
             }
         }
+        if (kRows == kRowsAhead && i0 == tid) load_rows(tid);  // (queued behind the loads the decision waits for)
 #pragma unroll
-        for (int j = 0; j < kNrBatch; ++j) {
+        for (int j = 0; j < kBatch; ++j) {
             const int i = i0 + j * kNrThreads;
             if (i < n) {
                 v = use_min ? fminf(v, uu[j]) : v + uu[j];
@@ -177,6 +227,7 @@ __global__ __launch_bounds__(kNrThreads) void nonrefresh_kernel(AppendArgs a, ui
             }
         }
     }
+    if (kRows == kRowsAhead && tid >= n) load_rows(tid);
 #pragma unroll
     for (int o = kWave / 2; o >= 1; o >>= 1) {
         const float w = __shfl_xor(v, o, kWave);
@@ -189,28 +240,34 @@ __global__ __launch_bounds__(kNrThreads) void nonrefresh_kernel(AppendArgs a, ui
         best[wave] = c;
     }
     __syncthreads();
+    // every wave adds the waves' results itself (lanes of equal index mod kNrWaves hold the same entry)
+    v = red[lane % kNrWaves];
+    c = best[lane % kNrWaves];
+#pragma unroll
+    for (int o = kNrWaves / 2; o >= 1; o >>= 1) {
+        const float w = __shfl_xor(v, o, kWave);
+        v = use_min ? fminf(v, w) : v + w;
+        const Cand x = shfl_xor_cand(c, o);
+        if (evicts_before(x, c)) c = x;
+    }
+    // one lane's result for all (utilities that tie at one position could leave the lanes apart)
+    v = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+    c = Cand{(uint32_t)__builtin_amdgcn_readfirstlane((int)c.key), __builtin_amdgcn_readfirstlane(c.pos),
+             __builtin_amdgcn_readfirstlane(c.idx)};
+    const float prior = n > 0 ? (use_min ? v : v / (float)n) : 0.0f;
+    int slot = n;  // room left: the newcomer is appended
+    if (n + 1 > budget) {
+        const Cand mine{float_key(prior), a.new_pos, n};
+        slot = evicts_before(mine, c) ? -1 : c.idx;
+    }
     if (tid == 0) {
-        float r = red[0];
-        c = best[0];
-        for (int w = 1; w < kNrWaves; ++w) {
-            r = use_min ? fminf(r, red[w]) : r + red[w];
-            if (evicts_before(best[w], c)) c = best[w];
-        }
-        const float prior = n > 0 ? (use_min ? r : r / (float)n) : 0.0f;
-        int slot = n;  // room left: the newcomer is appended
-        if (n + 1 > budget) {
-            const Cand mine{float_key(prior), a.new_pos, n};
-            slot = evicts_before(mine, c) ? -1 : c.idx;
-        }
         if (slot >= 0) {
             ub[slot] = prior;
             pb[slot] = a.new_pos;
         }
-        slot_out[b] = slot;
-        slot_sh = slot;
+        if (kRows == kRowsApart) slot_out[b] = slot;
     }
-    __syncthreads();
-    const int slot = slot_sh;
+    if (kRows == kRowsAhead && slot >= 0) store_rows(tid, slot);
     if (keep_out) {
         const int evicted = slot < 0 ? n : (slot < n ? slot : -1);
         for (int i = tid; i <= n; i += kNrThreads) keep_out[(size_t)b * a.cap + i] = i != evicted;
@@ -225,39 +282,10 @@ __global__ __launch_bounds__(kNrThreads) void nonrefresh_kernel(AppendArgs a, ui
             if (tid % nl == 0) a.norms[row * a.cap + slot] = nrm;
         }
     }
-    if (!copy_rows) return;
-    // rows r = (tensor, l, g) in [0, 2 L hkv), 16-byte chunk ch; quotients by float reciprocals (exact: the
-    // numerators are far below 2^22 and the +0.5 keeps them off integer boundaries)
-    const int lpr = a.row_bytes / 16;
-    const int total = a.layers * a.hkv * 2 * lpr;
-    const float inv_lpr = 1.0f / (float)lpr, inv_hkv = 1.0f / (float)a.hkv, inv_lg = 1.0f / (float)(a.layers * a.hkv);
-    constexpr int kCopy = 8;
+    if (kRows != kRowsAfter) return;
     for (int c0 = tid; c0 < total; c0 += kNrThreads * kCopy) {
-        u32x4 buf[kCopy];
-        size_t dsto[kCopy];
-#pragma unroll
-        for (int j = 0; j < kCopy; ++j) {
-            const int c = c0 + j * kNrThreads;
-            if (c < total) {
-                const int r = (int)(((float)c + 0.5f) * inv_lpr);
-                const int ch = c - r * lpr;
-                const int tensor = (int)(((float)r + 0.5f) * inv_lg);
-                const int lg = r - tensor * a.layers * a.hkv;
-                const int l = (int)(((float)lg + 0.5f) * inv_hkv);
-                const size_t row = ((size_t)l * a.batch + b) * a.hkv + (lg - l * a.hkv);
-                buf[j] = reinterpret_cast<const u32x4*>(static_cast<const char*>(tensor ? a.v_new : a.k_new) +
-                                                        row * a.row_bytes)[ch];
-                dsto[j] = ((row * a.cap + slot) * a.row_bytes) / 16 + ch + (tensor ? (size_t)1 << 62 : 0);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < kCopy; ++j) {
-            const int c = c0 + j * kNrThreads;
-            if (c < total) {
-                const bool isv = (dsto[j] >> 62) != 0;
-                reinterpret_cast<u32x4*>(isv ? a.v : a.k)[dsto[j] & (((size_t)1 << 62) - 1)] = buf[j];
-            }
-        }
+        load_rows(c0);
+        store_rows(c0, slot);
     }
 }
 
@@ -371,15 +399,20 @@ hipError_t launch_place(const PlaceArgs& a, hipStream_t s) {
 
 // Where the newcomer's rows are copied depends on the prior policy.  Under the minimum prior the newcomer
 // ties the lowest utility and, holding the newest position, is normally evicted at once: the decision kernel
-// copies the rows itself when needed (6.0 us per step at the 8B shape, against 8.0 with a second launch that
-// then has nothing to do).  Under the mean prior the newcomer is normally kept: one workgroup per sequence
-// copies 128 KB of rows slowly, a kernel over all rows does it in a fraction (8.6 us against 11.0).
+// copies the rows itself when needed.  Under the mean prior the newcomer is normally kept.  Its rows lie in as many
+// pages of the cache, which one workgroup writes slowly: with 128 KB per sequence (32 layers x 8 KV heads x 256
+// bytes) decision and copy in one kernel took 10.1 us, a second kernel over all rows and the decision 8.2; with
+// 39 KB (19 x 4) one kernel takes 6.7 us, two 8.3.  The line is drawn between, at 64 KiB.
 hipError_t launch_nonrefresh(const AppendArgs& a, uint8_t* keep_out, int budget, int* slot, hipStream_t s) {
-    const int copy_in_decision = a.init_mode == 2;
-    hipLaunchKernelGGL(nonrefresh_kernel, dim3(a.batch), dim3(kNrThreads), 0, s, a, keep_out, budget, slot,
-                       copy_in_decision);
+    const long long row_total = 2LL * a.layers * a.hkv * a.row_bytes;  // bytes of one sequence's newcomer rows
+    const int rows = a.init_mode == 2 ? kRowsAfter : row_total <= kAheadBytes ? kRowsAhead : kRowsApart;
+    const bool longer = a.n_in > kNrThreads * 4;
+    auto kern = rows == kRowsAfter   ? (longer ? nonrefresh_kernel<kRowsAfter, 16> : nonrefresh_kernel<kRowsAfter, 4>)
+                : rows == kRowsAhead ? (longer ? nonrefresh_kernel<kRowsAhead, 16> : nonrefresh_kernel<kRowsAhead, 4>)
+                                     : (longer ? nonrefresh_kernel<kRowsApart, 16> : nonrefresh_kernel<kRowsApart, 4>);
+    hipLaunchKernelGGL(kern, dim3(a.batch), dim3(kNrThreads), 0, s, a, keep_out, budget, slot);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || copy_in_decision) return e;
+    if (e != hipSuccess || rows != kRowsApart) return e;
     const long long threads = (long long)a.layers * a.batch * a.hkv * 2 * (a.row_bytes / 16);
     hipLaunchKernelGGL(newcomer_rows_kernel, dim3((unsigned)((threads + kThreads - 1) / kThreads)), dim3(kThreads), 0,
                        s, a, slot);

@@ -164,6 +164,62 @@ def test_vnorm_fused_into_the_merged_scorer_lockstep():
 
 
 @pytest.mark.parametrize("init", ["min", "mean"])
+@pytest.mark.parametrize("n,layers,hkv,d", [(1, 1, 1, 64), (1023, 1, 1, 64), (1025, 1, 1, 64), (4096, 1, 1, 64),
+                                             (4097, 1, 1, 64), (16384, 1, 1, 64), (16385, 1, 1, 64),
+                                             (70, 16, 8, 128), (70, 17, 8, 128), (70, 3, 5, 64)])
+def test_nonrefresh_step_edges(n, layers, hkv, d, init):
+    """A non-refresh step at the edges of its sweep (1,024 threads, 4 or 16 tokens each) and of where the newcomer's
+    rows are copied (64 KiB of them per sequence: 16 x 8 rows of 256 bytes twice, and one layer more), with room left
+    and at the budget.  The minimum is planted where the newcomer, of a mean prior, takes its slot."""
+    b, cap = 2, n + 2
+    gen = torch.Generator(device="cpu").manual_seed(n * 31 + layers)
+    rows = (layers, b, hkv, cap, d)
+    k = torch.randn(rows, generator=gen).to(torch.bfloat16)
+    v = torch.randn(rows, generator=gen).to(torch.bfloat16)
+    u0 = torch.rand(b, cap, generator=gen) + 0.5
+    low = [n - 1, n // 2]
+    for s, j in enumerate(low):
+        u0[s, j] = 0.25
+    pos0 = torch.stack([torch.randperm(cap, generator=gen) for _ in range(b)]).to(torch.int32)
+    new = torch.randn((2, layers, b, hkv, d), generator=gen).to(torch.bfloat16)
+    q = torch.zeros(layers, b, hkv, d, dtype=torch.bfloat16)
+    shape = B.make_shape(b, layers, hkv, hkv, d, cap, "bf16")
+    ws = B.workspace(shape, n + 1)
+    for budget in (n, n + 1):
+        print(f"non-refresh n={n} layers={layers} hkv={hkv} budget={budget} {init}", flush=True)
+        dk, dv, du, dp = k.cuda(), v.cuda(), u0.cuda(), pos0.cuda()
+        norms = torch.full(rows[:-1], -1.0, device="cuda")
+        B.kv_value_norms(shape, n, dv, norms)
+        keep = torch.full((b, cap), 9, dtype=torch.uint8, device="cuda")
+        params = B.make_params(0.9, budget, 4, False, init)
+        n_out = B.kv_evict_step(shape, params, 2, n, 10 * cap, q.cuda(), new[0].cuda(), new[1].cuda(), dk, dv, du, dp,
+                                ws, keep_out=keep, v_norms=norms)
+        torch.cuda.synchronize()
+        assert n_out == min(budget, n + 1)
+        kr, vr, ur, pr = k.clone(), v.clone(), u0.clone(), pos0.clone()
+        for s in range(b):
+            prior = float(u0[s, :n].double().mean()) if init == "mean" else 0.25
+            # the lowest prior ties the minimum and has the highest position: it leaves at once (so does a mean equal
+            # to the only utility)
+            slot = n if budget == n + 1 else (-1 if init == "min" or n == 1 else low[s])
+            want = [1] * (n + 1)
+            if budget == n:
+                want[n if slot < 0 else slot] = 0
+            assert keep[s, : n + 1].tolist() == want
+            if slot >= 0:
+                ur[s, slot], pr[s, slot] = prior, 10 * cap
+                kr[:, s, :, slot], vr[:, s, :, slot] = new[0][:, s], new[1][:, s]
+        assert_close(du[:, :n_out].cpu().numpy(), ur[:, :n_out].numpy(), "utilities", rel=1e-5)
+        assert torch.equal(dp[:, :n_out].cpu(), pr[:, :n_out])
+        assert torch.equal(dk[:, :, :, :n_out].cpu(), kr[:, :, :, :n_out])
+        assert torch.equal(dv[:, :, :, :n_out].cpu(), vr[:, :, :, :n_out])
+        fresh = torch.full_like(norms, -1.0)
+        B.kv_value_norms(shape, n_out, dv, fresh)
+        torch.cuda.synchronize()
+        assert torch.equal(norms[..., :n_out], fresh[..., :n_out])
+
+
+@pytest.mark.parametrize("init", ["min", "mean"])
 def test_nonrefresh_newcomer_kept_on_position_tie(init):
     """Non-refresh step where the newcomer survives: under the min prior it ties the lowest utility, and the
     cached token holding that utility has a higher position than the newcomer (positions need not grow), so
