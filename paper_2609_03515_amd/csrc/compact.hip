@@ -320,22 +320,33 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceArgs a) {
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int n = a.n;
     // this thread's 16-byte chunks of the newcomer's rows (tensor, KV head, chunk) are loaded first, so their
-    // latency overlaps the candidates' reduction
-    const int lpr = a.row_bytes / 16;
+    // latency overlaps the candidates' reduction; so are its utility and position, by the thread that moves them
+    const int lpr = a.row_bytes / 16, lsh = 31 - __clz(lpr);  // 8, 16 or 32 chunks per row
     const int total = 2 * a.hkv * lpr;
     constexpr int kPre = 2;
     u32x4 pre[kPre];
+    auto split = [&](int c, int& ch, bool& isv) __attribute__((always_inline)) {
+        const int r = c >> lsh;
+        ch = c & (lpr - 1);
+        isv = r >= a.hkv;
+        return ((size_t)l * a.batch + b) * a.hkv + (isv ? r - a.hkv : r);  // slab
+    };
     auto src_of = [&](int c) {
-        const int ch = c % lpr;
-        const int g = (c / lpr) % a.hkv;
-        const int tensor = c / (lpr * a.hkv);
-        const size_t slab = ((size_t)l * a.batch + b) * a.hkv + g;
-        return reinterpret_cast<const u32x4*>(static_cast<const char*>(tensor ? a.src_v : a.src_k) +
+        int ch;
+        bool isv;
+        const size_t slab = split(c, ch, isv);
+        return reinterpret_cast<const u32x4*>(static_cast<const char*>(isv ? a.src_v : a.src_k) +
                                               (slab * a.src_slab_rows + a.src_row0) * a.row_bytes) + ch;
     };
 #pragma unroll
     for (int j = 0; j < kPre; ++j)
         if (tid + j * kPlaceThreads < total) pre[j] = *src_of(tid + j * kPlaceThreads);
+    float u_new = 0.0f;
+    int p_new = 0;
+    if (l == 0 && tid == 0) {
+        u_new = a.u[(size_t)b * a.cap + n - 1];
+        p_new = a.pos[(size_t)b * a.cap + n - 1];
+    }
     int evicted = -1;
     if (n > a.budget) {
         const Cand* cb = a.cand + (size_t)b * a.ncand;
@@ -371,17 +382,15 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(PlaceArgs a) {
         }
     }
     if (l == 0 && tid == 0 && slot != n - 1) {
-        a.u[(size_t)b * a.cap + slot] = a.u[(size_t)b * a.cap + n - 1];
-        a.pos[(size_t)b * a.cap + slot] = a.pos[(size_t)b * a.cap + n - 1];
+        a.u[(size_t)b * a.cap + slot] = u_new;
+        a.pos[(size_t)b * a.cap + slot] = p_new;
     }
     // the source is the cache's own row n - 1 when src_row0 == n - 1 and src is the cache: nothing to move
     auto put = [&](int c, const u32x4& x) {
-        const int ch = c % lpr;
-        const int g = (c / lpr) % a.hkv;
-        const int tensor = c / (lpr * a.hkv);
-        const size_t slab = ((size_t)l * a.batch + b) * a.hkv + g;
-        u32x4* dst = reinterpret_cast<u32x4*>(static_cast<char*>(tensor ? a.v : a.k) + (slab * a.cap + slot) * a.row_bytes) +
-                     ch;
+        int ch;
+        bool isv;
+        const size_t slab = split(c, ch, isv);
+        u32x4* dst = reinterpret_cast<u32x4*>(static_cast<char*>(isv ? a.v : a.k) + (slab * a.cap + slot) * a.row_bytes) + ch;
         if (src_of(c) != dst) *dst = x;
     };
 #pragma unroll
