@@ -459,6 +459,7 @@ SelectArgs select_args(const kv_shape& s, const Layout& L, int n, int budget, co
     a.budget = budget;
     a.max_pairs = L.max_pairs;
     a.wide = select_wide_words(s.batch) ? at<uint32_t>(ws, L.wide_off) : nullptr;
+    a.wide_bins = at<uint32_t>(ws, L.pdst_off);
     return a;
 }
 
@@ -582,7 +583,7 @@ kv_status run_select_compact(const kv_shape& s, const Layout& L, int n, int budg
     SelectArgs a = select_args(s, L, n, budget, u, pos, ws);
     a.keep_out = keep_out;
     record(tr, 3, true, st);
-    rc = hip_status(launch_select(a, false, st));
+    rc = hip_status(launch_select(a, st));
     if (rc == KV_OK && traced) {
         ta.keep = keep_out;
         ta.raw_keep = rt->raw_keep ? rt->raw_keep : at<uint8_t>(ws, L.rmask_off);
@@ -591,10 +592,11 @@ kv_status run_select_compact(const kv_shape& s, const Layout& L, int n, int budg
         for (int which = 0; which < (ema_is_keep ? 1 : 2) && rc == KV_OK; ++which) {
             SelectArgs t = select_args(s, L, n, rt->k, which == 0 ? at<float>(ws, L.raw_off) : u, pos, ws);
             t.pair_dst = at<int32_t>(ws, L.tdst_off);
+            t.wide_bins = at<uint32_t>(ws, L.tdst_off);  // (the eviction's pairs stay)
             t.pair_src = at<int32_t>(ws, L.tsrc_off);
             t.npairs = at<int32_t>(ws, L.tnp_off);
             t.keep_out = const_cast<uint8_t*>(which == 0 ? ta.raw_keep : ta.ema_keep);
-            rc = hip_status(launch_select(t, false, st));
+            rc = hip_status(launch_select(t, st));
         }
         if (rc == KV_OK) rc = hip_status(launch_trace_stats(ta, false, st));
     }
@@ -801,7 +803,8 @@ kv_status kv_topk_select(const kv_shape* shape, int32_t n, int32_t budget, const
     if ((rc = check_ws(L, ws, ws_bytes)) != KV_OK) return rc;
     SelectArgs a = select_args(s, L, n, budget, u, pos, ws);
     a.keep_out = keep;
-    return hip_status(launch_select(a, false, static_cast<hipStream_t>(stream)));
+    a.pair_dst = a.pair_src = nullptr;  // the decision alone: no pairs are planned
+    return hip_status(launch_select(a, static_cast<hipStream_t>(stream)));
 }
 
 kv_status kv_compact(const kv_shape* shape, int32_t n, int32_t budget, const uint8_t* keep, void* k, void* v,
@@ -819,7 +822,7 @@ kv_status kv_compact(const kv_shape* shape, int32_t n, int32_t budget, const uin
     hipStream_t st = static_cast<hipStream_t>(stream);
     SelectArgs a = select_args(s, L, n, budget, u, pos, ws);
     a.keep_in = keep;
-    if ((rc = hip_status(launch_select(a, true, st))) != KV_OK) return rc;
+    if ((rc = hip_status(launch_plan(a, st))) != KV_OK) return rc;
     return hip_status(launch_move(move_args(s, L, n, budget, k, v, u, pos, v_norms, ws), st));
 }
 

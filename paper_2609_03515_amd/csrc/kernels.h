@@ -218,15 +218,18 @@ hipError_t launch_trace_stats(const TraceArgs& a, bool skip, hipStream_t s);
 struct SelectArgs {
     const float* u;
     const int32_t* pos;
-    const uint8_t* keep_in;  // plan-only mode: the retention decision to compact
+    const uint8_t* keep_in;  // launch_plan: the retention decision to compact
     uint8_t* keep_out;       // nullable: decision written here ([batch][cap])
-    int32_t* pair_dst;       // [batch][max_pairs]
+    int32_t* pair_dst;       // [batch][max_pairs] (nullable for launch_select: the decision alone)
     int32_t* pair_src;
     int32_t* npairs;         // [batch]
     int batch, cap, n, budget, max_pairs;
     uint32_t* wide;          // scratch of the multi-workgroup selection (select_wide_words words)
+    uint32_t* wide_bins;     // and [batch][max_pairs] words more (a pair list's place: the pairs are written last)
 };
-hipError_t launch_select(const SelectArgs& a, bool plan_only, hipStream_t s);
+hipError_t launch_select(const SelectArgs& a, hipStream_t s);
+// The pairs of the decision keep_in (n > budget).
+hipError_t launch_plan(const SelectArgs& a, hipStream_t s);
 // Scratch words of the multi-workgroup selection for a batch (0: that path is never taken for it).
 size_t select_wide_words(int batch);
 

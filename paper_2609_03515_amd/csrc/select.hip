@@ -85,7 +85,7 @@ struct RunCounter {
     }
 };
 
-__global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a, int plan_only) {
+__global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
     __shared__ SelShared sh;
     const int b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
@@ -94,14 +94,12 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a, int plan
     const int n = a.n, B = a.budget;
     const int k = min(B, n);
 
-    // decision: mode 0 keep all, 1 evict `winner`, 2 threshold (tau, pi), 3 read keep_in
+    // decision: mode 0 keep all, 1 evict `winner`, 2 threshold (tau, pi)
     int mode;
     int winner = -1;
     uint32_t tau = 0;
     int pi = 0x7fffffff;
-    if (plan_only) {
-        mode = 3;
-    } else if (n <= B) {
+    if (n <= B) {
         mode = 0;
     } else if (n == B + 1) {
         mode = 1;
@@ -205,18 +203,14 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a, int plan
         switch (mode) {
             case 0: return true;
             case 1: return i != winner;
-            case 2: {
+            default: {
                 const uint32_t key = float_key(ub[i]);
                 return key > tau || (key == tau && pb[i] <= pi);
             }
-            default: return a.keep_in[(size_t)b * a.cap + i] != 0;
         }
     };
 
-    int32_t* pdst = a.pair_dst + (size_t)b * a.max_pairs;
-    int32_t* psrc = a.pair_src + (size_t)b * a.max_pairs;
-
-    if (mode != 3 && a.keep_out) {
+    if (a.keep_out) {
         uint8_t* ko = a.keep_out + (size_t)b * a.cap;
         for (int i0 = tid; i0 < n; i0 += kThreads * kBatch) {
             bool kp[kBatch];
@@ -228,6 +222,9 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a, int plan
         }
     }
 
+    if (!a.pair_dst) return;  // the decision alone is wanted
+    int32_t* pdst = a.pair_dst + (size_t)b * a.max_pairs;
+    int32_t* psrc = a.pair_src + (size_t)b * a.max_pairs;
     if (mode == 0) {
         if (tid == 0) a.npairs[b] = 0;
         return;
@@ -354,25 +351,111 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a, int plan
     }
 }
 
+// ---- Plan of a given decision ---------------------------------------------------------------------------
+// The pairs of a retention mask (kv_compact): the ascending holes (dropped slots < k) and the ascending tails (kept
+// slots >= k), each at its rank.  Slots [0, k) and [k, n) are cut into slices of kPlanSlice, one workgroup each; a
+// workgroup counts what its region holds before its slice itself (the mask's bytes, four to a load, at most 128 KB
+// for a 131,073-token sequence), so one launch without any exchange does.  Workgroup 0 of a sequence counts both
+// regions for the pair count.  One workgroup per sequence that swept the mask twice, byte by byte, left kv_compact of
+// small rows at 30 us for 8 sequences of 32,769 slots and 85 for 2 of 131,073; now 12.7 and 14.6.
+constexpr int kPlanSlice = 4096;
+
+// Nonzero bytes of m[s, e), s <= e, over the workgroup (every thread gets the count; two barriers).
+__device__ unsigned count_kept(const uint8_t* m, int s, int e, unsigned* red) {
+    const int tid = threadIdx.x;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(m + s);
+    const int head = min(e - s, (int)((4 - at % 4) % 4));  // bytes before the first whole word
+    const int words = (e - s - head) / 4;
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(m + s + head);
+    unsigned c = 0;
+    auto kept = [](uint32_t x) { return (unsigned)__popc((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u); };
+    for (int i0 = tid; i0 < words; i0 += kThreads * kBatch) {
+        uint32_t x[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) x[j] = i0 + j * kThreads < words ? w[i0 + j * kThreads] : 0u;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) c += kept(x[j]);
+    }
+    const int rest = e - s - head - words * 4;  // bytes after the last whole word
+    if (tid < head) c += m[s + tid] != 0;
+    if (tid < rest) c += m[e - 1 - tid] != 0;
+#pragma unroll
+    for (int o = kWave / 2; o >= 1; o >>= 1) c += __shfl_xor(c, o, kWave);
+    if (tid % kWave == 0) red[tid / kWave] = c;
+    __syncthreads();
+    unsigned t = 0;
+#pragma unroll
+    for (int j = 0; j < kWaves; ++j) t += red[j];
+    __syncthreads();
+    return t;
+}
+
+__global__ __launch_bounds__(kThreads) void plan_kernel(SelectArgs a, int hole_slices) {
+    __shared__ unsigned red[kWaves];
+    constexpr int kGroups = kPlanSlice / kThreads;  // 64-slot groups per wave
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int n = a.n, k = min(a.budget, n);
+    const uint8_t* m = a.keep_in + (size_t)b * a.cap;
+    const bool tails = (int)blockIdx.x >= hole_slices;
+    const int first = tails ? k : 0, end = tails ? n : k;
+    const int lo = first + ((int)blockIdx.x - (tails ? hole_slices : 0)) * kPlanSlice, hi = min(end, lo + kPlanSlice);
+    // this wave's slots, loaded before the counts
+    const int base = lo + wave * kGroups * kWave;
+    bool mine[kGroups];  // a hole, or a tail
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        const int i = base + g * kWave + lane;
+        mine[g] = i < hi && (m[i] != 0) == tails;
+    }
+    unsigned before = count_kept(m, first, lo, red);
+    if (!tails) before = (unsigned)(lo - first) - before;
+    uint64_t mask[kGroups];
+    unsigned c = 0;
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        mask[g] = __ballot(mine[g]);
+        c += __popcll(mask[g]);
+    }
+    if (lane == 0) red[wave] = c;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) before += red[w];
+    int32_t* out = (tails ? a.pair_src : a.pair_dst) + (size_t)b * a.max_pairs;
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        const unsigned r = before + __popcll(mask[g] & below);
+        if (mine[g] && r < (unsigned)a.max_pairs) out[r] = base + g * kWave + lane;
+        before += __popcll(mask[g]);
+    }
+    if (blockIdx.x != 0) return;
+    __syncthreads();
+    const unsigned holes = (unsigned)k - count_kept(m, 0, k, red);
+    const unsigned kept = count_kept(m, k, n, red);
+    if (tid == 0) a.npairs[b] = (int)min(min(holes, kept), (unsigned)a.max_pairs);
+}
+
 // ---- Multi-workgroup selection: long sequences in a small batch ------------------------------------------
 // One workgroup per sequence leaves most of the chip idle when the batch is small and the sequences long (the
 // selection of a 128k-token first step at batch 2 took ~0.3 ms).  In the threshold case (n > B + 1) the same
 // radix select then runs as a short sequence of launches over P slices of every sequence:
-//   4 x (per-slice 256-bin histograms of the digit under the prefix found so far; one workgroup per sequence
-//   adds the slices' bins and picks the digit),
-//   one launch for ties at tau (the position select of the single-workgroup kernel; it returns at once unless
-//   more tokens tie at tau than are kept),
-//   per-slice hole and tail counts (and the decision, when asked for), then the pairs: every slice writes its
-//   holes and tails at the ranks that follow the slices before it.
-// The decisions and pairs are those of the single-workgroup kernel.  Scratch: P x 256 bins and P x 2 counts
-// per sequence, and a few state words (prefix, mask, remaining rank, tie count, position bound).
+//   4 x per-slice 256-bin histograms of the digit under the prefix found so far.  Each workgroup first takes the
+//   previous digit itself, from the bins that the previous launch left for every slice (two sets of bins, written
+//   in turn): a launch of its own for that, one workgroup per sequence, took as long as the histograms;
+//   one launch for the last digit and for ties at tau (the position select of the single-workgroup kernel; it is
+//   skipped unless more tokens tie at tau than are kept),
+//   per-slice hole and tail counts and the decision, when asked for, then (when the pairs are wanted) the pairs:
+//   every slice writes its holes and tails at the ranks that follow the slices before it.
+// kv_topk_select, which wants no pairs, back to back: 8 sequences of 32,769 tokens 35 -> 22 us, 2 of 131,073 51 -> 30.
+// The decisions and pairs are those of the single-workgroup kernel.  Scratch: P x 256 bins twice (the second set in
+// the first pair list, which is written last: n >= 1,024 P slots) and P x 2 counts per sequence, and a few state
+// words.
 __device__ __forceinline__ unsigned wave_sum_u(unsigned x) {
 #pragma unroll
     for (int o = kWave / 2; o >= 1; o >>= 1) x += __shfl_xor(x, o, kWave);
     return x;
 }
 
-constexpr int kWideThreads = 256;
+constexpr int kWideThreads = 512;
 constexpr int kWideMaxParts = 128;
 constexpr int kWideMinRows = 16384;  // shorter sequences keep the single-workgroup kernel
 constexpr int kWideSlice = 1024;     // fewest slots per slice
@@ -390,18 +473,34 @@ int wide_parts(int batch, int n) {
     return p < 4 ? 0 : p;
 }
 
+// Selection state of a sequence before a digit is taken: the digits found so far, the rank wanted among the keys
+// that have them, and how many keys have them.  Word 6 of the state: the position bound among ties.
+struct WideState {
+    uint32_t prefix;
+    unsigned krem, ties;
+};
+
 struct Wide {
-    unsigned* hist;  // [batch][P][256]
-    unsigned* cnt;   // [batch][P][2]
-    unsigned* st;    // [batch][kStateWords]: prefix, mask, remaining rank, ties at tau, position bound
+    unsigned* hist[2];  // [batch][P][256] each; hist[1] in rows of hist1_stride words per sequence
+    size_t hist1_stride;
+    unsigned* cnt;      // [batch][P][2]
+    unsigned* st;       // [batch][kStateWords]: two WideStates in turn, the position bound
     int P, slice;
     __device__ int lo(int p) const { return p * slice; }
+    __device__ unsigned* bins(int pass, int b) const {
+        return pass % 2 ? hist[1] + (size_t)b * hist1_stride : hist[0] + (size_t)b * P * 256;
+    }
+    __device__ WideState* state(int pass, int b) const {  // before digit `pass` (0: the leading one) is taken
+        return reinterpret_cast<WideState*>(st + (size_t)b * kStateWords) + pass % 2;
+    }
 };
 
 Wide wide_of(const SelectArgs& a, int P) {
     Wide w;
     const size_t pm = (size_t)wide_parts_max(a.batch);
-    w.hist = a.wide;
+    w.hist[0] = a.wide;
+    w.hist[1] = a.wide_bins;
+    w.hist1_stride = (size_t)a.max_pairs;
     w.cnt = a.wide + (size_t)a.batch * pm * 256;
     w.st = w.cnt + (size_t)a.batch * pm * 2;
     w.P = P;
@@ -409,14 +508,45 @@ Wide wide_of(const SelectArgs& a, int P) {
     return w;
 }
 
-__global__ __launch_bounds__(kWideThreads) void wide_hist_kernel(SelectArgs a, Wide w, int shift) {
+// The state after digit `pass` from the bins every slice left for it (every thread gets it; all kN threads call).
+template <int kN>
+__device__ WideState wide_digit(SelShared& sh, const SelectArgs& a, const Wide& w, int b, int pass) {
+    const int tid = threadIdx.x, bin = tid % 256;
+    constexpr int kParts = kN / 256, kAhead = 16;
+    const WideState old = pass == 0 ? WideState{0u, (unsigned)a.budget, 0u} : *w.state(pass, b);
+    const unsigned* hb = w.bins(pass, b) + bin;
+    unsigned c = 0;
+    for (int p0 = tid / 256; p0 < w.P; p0 += kParts * kAhead) {
+        unsigned x[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) x[j] = p0 + j * kParts < w.P ? hb[(size_t)(p0 + j * kParts) * 256] : 0u;
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) c += x[j];
+    }
+    if (tid < 256) sh.hist[tid] = 0;
+    __syncthreads();
+    atomicAdd(&sh.hist[bin], c);
+    __syncthreads();
+    find_digit(sh, old.krem, true);
+    __syncthreads();
+    return WideState{old.prefix | (sh.bcast[0] << (24 - 8 * pass)), old.krem - sh.bcast[1], sh.bcast[2]};
+}
+
+__global__ __launch_bounds__(kWideThreads) void wide_hist_kernel(SelectArgs a, Wide w, int pass) {
+    __shared__ SelShared sh;
     __shared__ unsigned hist[256];
     const int p = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    const unsigned* st = w.st + (size_t)b * kStateWords;
-    const uint32_t prefix = shift == 24 ? 0u : st[0], pmask = shift == 24 ? 0u : st[1];
+    const int shift = 24 - 8 * pass;
     const float* ub = a.u + (size_t)b * a.cap;
     const int lo = w.lo(p), hi = min(a.n, lo + w.slice);
-    hist[tid] = 0;
+    if (tid < 256) hist[tid] = 0;
+    uint32_t prefix = 0;
+    if (pass > 0) {
+        const WideState st = wide_digit<kWideThreads>(sh, a, w, b, pass - 1);
+        prefix = st.prefix;
+        if (p == 0 && tid == 0) *w.state(pass, b) = st;  // (the slices read state(pass - 1))
+    }
+    const uint32_t pmask = pass == 0 ? 0u : 0xffffffffu << (shift + 8);
     __syncthreads();
     RunCounter rc;
     for (int i0 = lo + tid; i0 < hi; i0 += kWideThreads * kBatch) {
@@ -432,49 +562,24 @@ __global__ __launch_bounds__(kWideThreads) void wide_hist_kernel(SelectArgs a, W
     }
     rc.flush(hist);
     __syncthreads();
-    w.hist[((size_t)b * w.P + p) * 256 + tid] = hist[tid];
+    if (tid < 256) w.bins(pass, b)[(size_t)p * 256 + tid] = hist[tid];
 }
 
-__global__ __launch_bounds__(kWideThreads) void wide_digit_kernel(SelectArgs a, Wide w, int shift) {
-    __shared__ SelShared sh;
-    const int b = blockIdx.x, tid = threadIdx.x;
-    unsigned* st = w.st + (size_t)b * kStateWords;
-    // the slices' bins, eight loads in flight per thread
-    const unsigned* hb = w.hist + (size_t)b * w.P * 256 + tid;
-    unsigned c = 0;
-    int p = 0;
-    for (; p + 8 <= w.P; p += 8) {
-        unsigned x[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = hb[(size_t)(p + j) * 256];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) c += x[j];
-    }
-    for (; p < w.P; ++p) c += hb[(size_t)p * 256];
-    sh.hist[tid] = c;
-    const unsigned krem = shift == 24 ? (unsigned)a.budget : st[2];
-    __syncthreads();
-    find_digit(sh, krem, true);
-    __syncthreads();
-    if (tid == 0) {
-        st[0] = (shift == 24 ? 0u : st[0]) | (sh.bcast[0] << shift);
-        st[1] = (shift == 24 ? 0u : st[1]) | (255u << shift);
-        st[2] = krem - sh.bcast[1];
-        st[3] = sh.bcast[2];
-    }
-}
-
-// Ties at tau: the krem lowest positions among them are kept (position radix select, one workgroup).
+// The last digit, and ties at tau: the krem lowest positions among them are kept (position radix select, one
+// workgroup).
 __global__ __launch_bounds__(kThreads) void wide_ties_kernel(SelectArgs a, Wide w) {
     __shared__ SelShared sh;
     const int b = blockIdx.x, tid = threadIdx.x;
     unsigned* st = w.st + (size_t)b * kStateWords;
-    const uint32_t tau = st[0];
-    unsigned krem = st[2];
-    if (krem >= st[3]) {
-        if (tid == 0) st[4] = 0x7fffffffu;
+    const WideState last = wide_digit<kThreads>(sh, a, w, b, 3);
+    const uint32_t tau = last.prefix;
+    unsigned krem = last.krem;
+    if (tid == 0) *w.state(4, b) = last;
+    if (krem >= last.ties) {
+        if (tid == 0) st[6] = 0x7fffffffu;
         return;
     }
+    __syncthreads();
     const float* ub = a.u + (size_t)b * a.cap;
     const int32_t* pb = a.pos + (size_t)b * a.cap;
     uint32_t pp = 0, pm = 0;
@@ -496,13 +601,14 @@ __global__ __launch_bounds__(kThreads) void wide_ties_kernel(SelectArgs a, Wide 
         krem -= sh.bcast[1];
         __syncthreads();
     }
-    if (tid == 0) st[4] = pp;
+    if (tid == 0) st[6] = pp;
 }
 
 __device__ __forceinline__ bool wide_keep(const SelectArgs& a, const Wide& w, int b, int i) {
-    const unsigned* st = w.st + (size_t)b * kStateWords;
+    const uint32_t tau = w.state(4, b)->prefix;
+    const int bound = (int)w.st[(size_t)b * kStateWords + 6];
     const uint32_t key = float_key(a.u[(size_t)b * a.cap + i]);
-    return key > st[0] || (key == st[0] && a.pos[(size_t)b * a.cap + i] <= (int)st[4]);
+    return key > tau || (key == tau && a.pos[(size_t)b * a.cap + i] <= bound);
 }
 
 // Per slice: holes (dropped slots < k) and tails (kept slots >= k), and the decision when asked for.
@@ -616,21 +722,27 @@ size_t select_wide_words(int batch) {
     return pm ? (size_t)batch * (pm * 258 + kStateWords) : 0;
 }
 
-hipError_t launch_select(const SelectArgs& a, bool plan_only, hipStream_t s) {
+hipError_t launch_plan(const SelectArgs& a, hipStream_t s) {
+    const int k = a.budget < a.n ? a.budget : a.n;
+    const int hole_slices = (k + kPlanSlice - 1) / kPlanSlice, tail_slices = (a.n - k + kPlanSlice - 1) / kPlanSlice;
+    if (a.batch > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(plan_kernel, dim3(hole_slices + tail_slices, a.batch), dim3(kThreads), 0, s, a, hole_slices);
+    return hipGetLastError();
+}
+
+hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
     const int P = a.wide ? wide_parts(a.batch, a.n) : 0;
-    if (plan_only || a.n <= a.budget + 1 || P == 0) {
-        hipLaunchKernelGGL(select_kernel, dim3(a.batch), dim3(kThreads), 0, s, a, plan_only ? 1 : 0);
+    if (a.n <= a.budget + 1 || P == 0) {
+        hipLaunchKernelGGL(select_kernel, dim3(a.batch), dim3(kThreads), 0, s, a);
         return hipGetLastError();
     }
     const Wide w = wide_of(a, P);
     const dim3 sliced(P, a.batch);
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(wide_hist_kernel, sliced, dim3(kWideThreads), 0, s, a, w, shift);
-        hipLaunchKernelGGL(wide_digit_kernel, dim3(a.batch), dim3(kWideThreads), 0, s, a, w, shift);
-    }
+    for (int pass = 0; pass < 4; ++pass)
+        hipLaunchKernelGGL(wide_hist_kernel, sliced, dim3(kWideThreads), 0, s, a, w, pass);
     hipLaunchKernelGGL(wide_ties_kernel, dim3(a.batch), dim3(kThreads), 0, s, a, w);
     hipLaunchKernelGGL(wide_count_kernel, sliced, dim3(kWideThreads), 0, s, a, w);
-    hipLaunchKernelGGL(wide_plan_kernel, sliced, dim3(kWideThreads), 0, s, a, w);
+    if (a.pair_dst) hipLaunchKernelGGL(wide_plan_kernel, sliced, dim3(kWideThreads), 0, s, a, w);
     return hipGetLastError();
 }
 

@@ -167,3 +167,37 @@ def test_compact_parity(case):
                 np.testing.assert_array_equal(kgr[l, b, h, kk:], kr[l, b, h, kk:])   # untouched beyond k
         np.testing.assert_array_equal(ug.cpu()[b, :kk].numpy(), compact_rows(u[b, :n].numpy(), kb, budget)[:kk])
         np.testing.assert_array_equal(pg.cpu()[b, :kk].numpy(), compact_rows(pos[b, :n].numpy(), kb, budget)[:kk])
+
+
+@pytest.mark.parametrize("n,budget", [(2, 1), (4096, 4095), (4097, 4096), (8193, 4096), (8192, 4097), (9000, 1),
+                                      (33000, 20000), (131073, 5)])
+def test_compact_plan_edges(n, budget):
+    """The compaction's pairs at the edges of the plan's 4,096-slot slices, with masks at every byte alignment, kept
+    marked by any nonzero byte, and a sequence that keeps fewer tokens than the budget (the pairs then end with the
+    shorter list)."""
+    batch, hkv, d = 5, 1, 64
+    cap = n + 3                                     # the sequences' masks start at different alignments
+    gen = torch.Generator(device="cpu").manual_seed(n + budget)
+    keep = torch.zeros(batch, cap, dtype=torch.uint8)
+    for b in range(batch):
+        count = budget if b else max(1, budget - 3)
+        keep[b, torch.randperm(n, generator=gen)[:count]] = [1, 1, 255, 2, 128][b]
+    keep[:, n:] = 1                                 # past the cached rows: not read
+    rows = torch.arange(batch * cap * d, dtype=torch.int32).reshape(1, batch, hkv, cap, d)
+    k = rows.to(torch.float32)
+    u = torch.rand(batch, cap, generator=gen)
+    pos = torch.stack([torch.randperm(cap, generator=gen) for _ in range(batch)]).to(torch.int32)
+    shape = B.make_shape(batch, 1, hkv, hkv, d, cap, "f32")
+    ws = B.workspace(shape, n)
+    kg, vg, ug, pg = k.cuda(), k.cuda(), u.cuda(), pos.cuda()
+    print(f"compact plan n={n} budget={budget}", flush=True)
+    B.kv_compact(shape, n, budget, keep.cuda(), kg, vg, ug, pg, ws)
+    torch.cuda.synchronize()
+    for b in range(batch):
+        kept = keep[b, :n].numpy() != 0
+        holes, tails = np.nonzero(~kept[:budget])[0], budget + np.nonzero(kept[budget:])[0]
+        m = min(len(holes), len(tails))
+        want = np.arange(n)
+        want[holes[:m]] = tails[:m]
+        assert torch.equal(kg[0, b, 0, :n].cpu(), k[0, b, 0][want]) and torch.equal(vg, kg)
+        assert torch.equal(ug[b, :n].cpu(), u[b][want]) and torch.equal(pg[b, :n].cpu(), pos[b][want])
