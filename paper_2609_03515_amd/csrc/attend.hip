@@ -52,69 +52,85 @@ __device__ __forceinline__ void read_probs(const float* src, float (&e)[GP]) {
     }
 }
 
-// Several chunks per slab: a combine kernel after the chunks' launch, combine_parts() workgroups per slab.  With
+// Several chunks per slab: a combine kernel after the chunks' launch, as many workgroups.  With
 //   f_h(c) = exp(m_c - M_h) / S_h,  M_h = max_c m_c,  S_h = sum_c exp(m_c - M_h) S_c
-// workgroup 0 of a slab adds the outputs, o_h = sum_c f_h(c) o_c, and, when emitting, workgroup 1 + p the scores of
-// rows [p kCombineRows, (p + 1) kCombineRows), r(row) = sum_{h in group} f_h(c) e_h(row) from the exponentials
-// e_h = exp(z_h - m_c) that the chunks wrote (c: the row's chunk).
+// the slab's first workgroup adds the outputs, o_h = sum_c f_h(c) o_c (upper half of its threads), and, when emitting,
+// every workgroup takes the scores of its chunk's rows (lower half), r(row) = sum_{h in group} f_h(c) e_h(row), from
+// the exponentials e_h = exp(z_h - m_c) that the chunk wrote.
 // The kernel moves little and is bound by its chain of memory latencies, so every thread issues all of its loads
 // (partial outputs of up to kAhead chunks, or the GP exponentials of its four rows) before the statistics are
-// taken, those come from one load per (head, chunk) staged in LDS, and outputs and rows are separate workgroups.
-// It had taken the chunks' pairs, then the outputs and the heads' rows in turn, one latency each.
+// taken, and those are one load per (head, chunk) and a reduction over the lanes of a row.  It had taken the chunks'
+// pairs, then the outputs and the heads' rows in turn, one latency each.  The workgroups are numbered like the
+// chunks', so that a chunk's exponentials are read by the XCD whose L2 wrote them:
+// 28 layer calls of 32 sequences x 4 KV heads x 2,049 rows (7 heads each, 2 chunks) 884 -> 818 us, 32 of 8 x 8 x 3,278
+// (4 heads, 4 chunks) 793 -> 782, against rows in parts of 2,048 and a workgroup of their own for the outputs
+// (short chunks in parts of 1,024 rows: one sequence of the latter shape, 13 chunks, 427 against 413).
 // Electing the last chunk of a slab inside the attention kernel instead was measured twice at the 8B shape:
 // with a device-scope release/acquire fence in every chunk (a full L2 write-back and invalidate) 5x slower per
 // layer; with the partials written and read back by device-scope (write-through) accesses and a completion
 // wait before the arrival count, no faster without the score (the chunk's store, count and reload round trips
 // cost what the kernel boundary does) and 9% slower with it (one workgroup per slab takes the score's rows).
 constexpr int kCombineThreads = 512;
-constexpr int kCombineRows = kCombineThreads * 4;
-constexpr int kCombineStaged = 1024;  // (head, chunk) pairs staged in LDS; more are taken from memory where needed
-__host__ __device__ constexpr int combine_parts(int n, bool emit) {
-    return 1 + (emit ? (n + kCombineRows - 1) / kCombineRows : 0);
-}
+constexpr int kCombineHalf = kCombineThreads / 2;
+// workgroups per slab: one per chunk, or one without scores
+__host__ __device__ constexpr int combine_parts(int nchunk, bool emit) { return emit ? nchunk : 1; }
 
 template <typename T, int D, int GP, int kAhead>
 __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(ScoreArgs a) {
-    __shared__ float2 pairs[kCombineStaged];
-    __shared__ float fs[kCombineStaged];
+    __shared__ float fs[GP * kWave];
     __shared__ float cm[GP], ci[GP];  // more chunks than are staged: M_h and 1 / S_h
-    const int parts = combine_parts(a.n, a.emit);
-    const int s = blockIdx.x / parts;  // slab: (l * batch + b) * hkv + g, l relative to the call
-    const int part = blockIdx.x % parts;
     const int tid = threadIdx.x, nchunk = a.nchunk, group = a.group;
+    const int parts = combine_parts(nchunk, a.emit);
+    const int s = blockIdx.x / parts;  // slab: (l * batch + b) * hkv + g, l relative to the call
+    const int chunk = blockIdx.x % parts;
     const size_t head0 = (size_t)(s / a.hkv) * a.hq + (size_t)(s % a.hkv) * group;
     const float2* pp = a.part + head0 * nchunk;  // [head][chunk]
-    const int npairs = group * nchunk;
-    const bool staged = npairs <= kCombineStaged;
+    const bool staged = nchunk <= kWave;
 
-    // this thread's loads: four outputs of one head over the first chunks, or four rows of every head
+    // this thread's loads: four rows of every head, or four outputs of one head over the first chunks
+    const bool outputs = tid >= kCombineHalf;
+    const int row_end = min(a.n, (chunk + 1) * a.chunk_rows);  // (rows up to the padded stride are scratch)
+    int row = chunk * a.chunk_rows + (outputs ? 0 : tid) * 4;
     constexpr int kQuads = D / 4;
-    const int h0 = tid / kQuads, d0 = tid % kQuads * 4;
-    auto out_of = [&](int h, int c) __attribute__((always_inline)) {
-        return *reinterpret_cast<const f32x4*>(a.opart + ((head0 + h) * nchunk + c) * D + d0);
+    int quad = tid - kCombineHalf;
+    const int quad_end = chunk == 0 ? group * kQuads : 0;
+    auto out_of = [&](int q, int c) __attribute__((always_inline)) {
+        return *reinterpret_cast<const f32x4*>(a.opart + ((head0 + q / kQuads) * nchunk + c) * D + q % kQuads * 4);
     };
-    const int row = (part - 1) * kCombineRows + tid * 4;  // rows >= n up to the padded stride are scratch
     f32x4 x[GP > kAhead ? GP : kAhead];
-    if (part == 0) {
+    auto load_outputs = [&](int c0) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < kAhead; ++c)
-            if (h0 < group && c < nchunk) x[c] = out_of(h0, c);
-    } else if (row < a.n) {
+            if (c0 + c < nchunk) x[c] = out_of(quad, c0 + c);
+    };
+    auto load_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < GP; ++h)
             if (h < group) x[h] = *reinterpret_cast<const f32x4*>(a.z + (head0 + h) * a.n_stride + row);
+    };
+    if (outputs) {
+        if (quad < quad_end) load_outputs(0);
+    } else if (a.emit && row < row_end) {
+        load_rows();
     }
 
-    if (staged) {
-        for (int i = tid; i < npairs; i += kCombineThreads) pairs[i] = pp[i];
-        __syncthreads();
-        for (int i = tid; i < npairs; i += kCombineThreads) {
-            const float2* ph = pairs + i / nchunk * nchunk;
-            float mx = ph[0].x;
-            for (int c = 1; c < nchunk; ++c) mx = fmaxf(mx, ph[c].x);
-            float tot = 0.0f;
-            for (int c = 0; c < nchunk; ++c) tot = fmaf(__expf(ph[c].x - mx), ph[c].y, tot);
-            fs[i] = tot > 0.0f ? __expf(pairs[i].x - mx) / tot : 0.0f;
+    // one (head, chunk) pair per lane: a row of 16 lanes per head, or a wave; more chunks than that are taken from
+    // memory again where needed
+    if (nchunk <= 16) {
+        const int h = tid / 16, c = tid % 16;
+        if (h < group) {
+            const float2 p = c < nchunk ? pp[h * nchunk + c] : make_float2(-INFINITY, 0.0f);
+            const float w = __expf(p.x - row_allmax(p.x));
+            const float tot = group_allsum<16>(w * p.y);
+            if (c < nchunk) fs[h * nchunk + c] = tot > 0.0f ? w / tot : 0.0f;
+        }
+    } else if (staged) {
+        const int c = tid % kWave;
+        for (int h = tid / kWave; h < group; h += kCombineThreads / kWave) {
+            const float2 p = c < nchunk ? pp[h * nchunk + c] : make_float2(-INFINITY, 0.0f);
+            const float w = __expf(p.x - wave_max(p.x));
+            const float tot = wave_sum(w * p.y);
+            if (c < nchunk) fs[h * nchunk + c] = tot > 0.0f ? w / tot : 0.0f;
         }
     } else if (tid < group) {
         const float2* ph = pp + (size_t)tid * nchunk;
@@ -129,36 +145,38 @@ __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(ScoreAr
         return staged ? fs[h * nchunk + c] : __expf(pp[(size_t)h * nchunk + c].x - cm[h]) * ci[h];
     };
 
-    if (part != 0) {
-        if (row >= a.n) return;
-        const int c = row / a.chunk_rows;  // four rows lie in one chunk: chunks are a multiple of 4 rows
-        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (!outputs) {
+        if (!a.emit) return;
+        float f[GP];
 #pragma unroll
-        for (int h = 0; h < GP; ++h)
-            if (h < group) acc += x[h] * factor(h, c);
-        *reinterpret_cast<f32x4*>(a.r + (size_t)s * a.n_stride + row) = acc;
+        for (int h = 0; h < GP; ++h) f[h] = h < group ? factor(h, chunk) : 0.0f;
+        for (bool first = true; row < row_end; row += kCombineHalf * 4, first = false) {
+            if (!first) load_rows();
+            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int h = 0; h < GP; ++h)
+                if (h < group) acc += x[h] * f[h];
+            *reinterpret_cast<f32x4*>(a.r + (size_t)s * a.n_stride + row) = acc;
+        }
         return;
     }
-    if (a.emit_norms && tid / kWave == kCombineThreads / kWave - 1) {
+    if (a.emit_norms && chunk == 0 && tid / kWave == kCombineThreads / kWave - 1) {
         float tot = 0.0f;
         for (int c = tid % kWave; c < nchunk; c += kWave) tot += a.npart[(size_t)s * nchunk + c];
         tot = wave_sum(tot);
         if (tid % kWave == 0) a.vinv[s] = tot > 0.0f ? (float)a.n / tot : 0.0f;
     }
     T* ob = static_cast<T*>(a.o) + head0 * D;
-    for (int h = h0; h < group; h += kCombineThreads / kQuads) {
+    for (bool first = true; quad < quad_end; quad += kCombineHalf, first = false) {
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int c0 = 0; c0 < nchunk; c0 += kAhead) {
-            if (h != h0 || c0 != 0)
-#pragma unroll
-                for (int c = 0; c < kAhead; ++c)
-                    if (c0 + c < nchunk) x[c] = out_of(h, c0 + c);
+            if (!first || c0 != 0) load_outputs(c0);
 #pragma unroll
             for (int c = 0; c < kAhead; ++c)
-                if (c0 + c < nchunk) acc += x[c] * factor(h, c0 + c);
+                if (c0 + c < nchunk) acc += x[c] * factor(quad / kQuads, c0 + c);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) Elem<T>::store(ob + h * D + d0 + j, acc[j]);
+        for (int j = 0; j < 4; ++j) Elem<T>::store(ob + quad * 4 + j, acc[j]);
     }
 }
 
@@ -761,7 +779,7 @@ hipError_t launch_attend_gp(const ScorePlan& plan, const ScoreArgs& a, hipStream
             // more than eight chunks' partial outputs in flight only where there are more (one sequence of 8 KV heads x
             // 3,278 rows, 13 chunks: 424 -> 416 us for 32 layer calls; with 4 chunks the registers cost 0.2%)
             auto combine = plan.nchunk > 8 ? attend_combine_kernel<T, D, GP, 16> : attend_combine_kernel<T, D, GP, 8>;
-            hipLaunchKernelGGL(combine, dim3(plan.grid / plan.nchunk * combine_parts(a.n, a.emit)),
+            hipLaunchKernelGGL(combine, dim3(plan.grid / plan.nchunk * combine_parts(plan.nchunk, a.emit)),
                                dim3(kCombineThreads), 0, s, a);
         }
         return hipGetLastError();

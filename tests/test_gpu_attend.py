@@ -238,6 +238,33 @@ def test_attend_value_pass_edges(group, n):
     assert np.all(np.abs(got2 - got)[same] <= (4e-4 * scale + 2.0 ** -7 * np.abs(ref))[same])
 
 
+@pytest.mark.parametrize("hq,hkv,n", [(1, 1, 4096), (16, 1, 4100), (7, 1, 4361), (1, 1, 8192), (3, 1, 16384),
+                                      (16, 1, 90000), (3, 1, 331000)])
+def test_attend_chunk_counts(hq, hkv, n):
+    """The combine's ways of taking the chunks' statistics: up to 16 chunks per slab (16, 17 and 18 here), up to 64
+    (32 and 64) and more (71 and 65: the LDS of one chunk holds 1,280 or 5,120 rows).  Bounds as in the geometries
+    above (the oracle's own tolerance)."""
+    d = 128
+    gen = torch.Generator(device="cpu").manual_seed(n)
+    k = torch.randn(1, 1, hkv, n, d, generator=gen).to(torch.bfloat16)
+    v = torch.randn(1, 1, hkv, n, d, generator=gen).to(torch.bfloat16)
+    q = torch.randn(1, 1, hq, d, generator=gen).to(torch.bfloat16)
+    pos = torch.arange(n, dtype=torch.int32).repeat(1, 1).contiguous()
+    shape = B.make_shape(1, 1, hq, hkv, d, n, "bf16")
+    ws = B.workspace(shape, n)
+    dk, dv, dq, dpos = k.cuda(), v.cuda(), q.cuda(), pos.cuda()
+    o, u = torch.empty_like(dq), torch.zeros(1, n, device="cuda")
+    s_out = torch.empty(1, 1, n, device="cuda")
+    print(f"attend chunks hq={hq} n={n}", flush=True)
+    B.kv_attend_score(shape, 0, 1, n, dq, dk, dv, dpos, n - 1, 0.0, 0, B.KV_EMIT_SCORES, o, ws)
+    B.kv_evict_finish(shape, B.make_params(0.5, n), 1, n, dk, dv, u, dpos, ws, s_out=s_out)
+    torch.cuda.synchronize()
+    keys, ql, pr = to_f64(raw_numpy(k)[0, 0], "bf16"), to_f64(raw_numpy(q)[0, 0], "bf16"), np.arange(n)
+    ref, scale = attention_output(ql, keys, to_f64(raw_numpy(v)[0, 0], "bf16"), pr, n - 1, 0.0, 0)
+    assert_o(o, ref[None, None], scale[None, None], "bf16", "outputs")
+    assert_close(s_out.cpu().numpy(), layer_scores(ql, keys, pr, n - 1, 0.0, 0)[None, None], "scores")
+
+
 @pytest.mark.parametrize("merge,entropy", [(0, False), (1, False), (2, False), (4, False), (8, False), (4, True)],
                          ids=["auto", "merge1", "merge2", "merge4", "merge8", "merge4_entropy"])
 def test_fused_scores_equal_separate_pass_bitwise(merge, entropy):
