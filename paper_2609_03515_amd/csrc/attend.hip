@@ -75,14 +75,26 @@ constexpr int kCombineHalf = kCombineThreads / 2;
 // workgroups per slab: one per chunk, or one without scores
 __host__ __device__ constexpr int combine_parts(int nchunk, bool emit) { return emit ? nchunk : 1; }
 
+// Slab and chunk of workgroup `block` of `slabs` x `chunks`: the chunks of a slab are eight workgroups apart, so that
+// the XCDs, which take workgroups in turn, each hold whole slabs (a last group of fewer than eight slabs: in order).
+struct SlabChunk {
+    int s, c;
+};
+__device__ __forceinline__ SlabChunk slab_chunk(int block, int slabs, int chunks) {
+    constexpr int kXcds = 8;
+    const int full = slabs / kXcds * kXcds * chunks;
+    if (block >= full) return {block / chunks, block % chunks};
+    const int r = block % (kXcds * chunks);
+    return {block / (kXcds * chunks) * kXcds + r % kXcds, r / kXcds};
+}
+
 template <typename T, int D, int GP, int kAhead>
 __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(ScoreArgs a) {
     __shared__ float fs[GP * kWave];
     __shared__ float cm[GP], ci[GP];  // more chunks than are staged: M_h and 1 / S_h
     const int tid = threadIdx.x, nchunk = a.nchunk, group = a.group;
-    const int parts = combine_parts(nchunk, a.emit);
-    const int s = blockIdx.x / parts;  // slab: (l * batch + b) * hkv + g, l relative to the call
-    const int chunk = blockIdx.x % parts;
+    const SlabChunk sc = slab_chunk(blockIdx.x, a.layers * a.batch * a.hkv, combine_parts(nchunk, a.emit));
+    const int s = sc.s, chunk = sc.c;  // slab: (l * batch + b) * hkv + g, l relative to the call
     const size_t head0 = (size_t)(s / a.hkv) * a.hq + (size_t)(s % a.hkv) * group;
     const float2* pp = a.part + head0 * nchunk;  // [head][chunk]
     const bool staged = nchunk <= kWave;
@@ -289,6 +301,7 @@ void attend_kernel(ScoreArgs a) {
     // the waves' partial outputs are added in one step when every wave's slice fits 16 KiB of LDS (GP * D <= 512
     // floats: groups up to 4 at d = 128), else wave by wave (one barrier each); the sums are the same
     constexpr bool kMV = kV && use_mfma_v<T, D, GP>();
+    constexpr bool kFirstV = kV && (kMV || kNbuf == 2);
     constexpr bool kWaveSlices = kWaves * GP * D <= 4096 && !kMV;
     constexpr int kMVSlices = GP > 8 ? kWaves / 2 : kWaves;  // matrix-core form: at most 32 KiB of slices
     extern __shared__ float zs[];
@@ -298,8 +311,8 @@ void attend_kernel(ScoreArgs a) {
 
     const L ln;
     const KP kp;
-    const int chunk = blockIdx.x % a.nchunk;
-    const int s = blockIdx.x / a.nchunk;  // slab: (l * batch + b) * hkv + g, l relative to the call
+    const SlabChunk sc = slab_chunk(blockIdx.x, a.layers * a.batch * a.hkv, a.nchunk);
+    const int chunk = sc.c, s = sc.s;  // slab: (l * batch + b) * hkv + g, l relative to the call
     const int g = s % a.hkv;
     const int lb = s / a.hkv;
     const int b = lb % a.batch;
@@ -312,10 +325,14 @@ void attend_kernel(ScoreArgs a) {
     const __amdgpu_buffer_rsrc_t vrs = raw_rsrc(static_cast<const T*>(a.v) + base, nrows * L::kRowBytes);
     const __amdgpu_buffer_rsrc_t prs = raw_rsrc(a.pos + (size_t)b * a.cap + row0, nrows * 4);
 
-    if (threadIdx.x == 0) {
-        next_unit[0] = 0;
-        next_unit[1] = 0;
-    }
+    // the first unit of a wave is its own index, in both passes: its loads wait for no claim and no barrier (the same
+    // decode steps 812, 758 and 398 us with every unit claimed, 801, 744 and 387 so)
+    constexpr bool kFirstK = kNbufK == 2;
+    typename KP::max_t mk = kp.max_init();
+    typename KP::buf_t kbuf[kNbufK];
+    int pbuf[kNbufK];
+    if (kFirstK && ln.wave < nku) kp.load(krs, prs, ln.wave, kbuf[0], pbuf[0]);
+    if (threadIdx.x < 2) next_unit[threadIdx.x] = threadIdx.x == 0 ? (kFirstK ? kWaves : 0) : (kFirstV ? kWaves : 0);
     typename KP::q_t qv;
     kp.load_q(a, (size_t)lb, g, qv);
     __syncthreads();
@@ -326,15 +343,10 @@ void attend_kernel(ScoreArgs a) {
     };
 
     // 1. K pass
-    typename KP::max_t mk = kp.max_init();
-    {
-        typename KP::buf_t kbuf[kNbufK];
-        int pbuf[kNbufK];
-        claimed_units<kNbufK>(
-            nku, -1, [&]() __attribute__((always_inline)) { return claim(0); },
-            [&](auto slot, int u) __attribute__((always_inline)) { kp.load(krs, prs, u, kbuf[slot], pbuf[slot]); },
-            [&](auto slot, int u) __attribute__((always_inline)) { kp.logits(a, kbuf[slot], qv, pbuf[slot], u, nrows, zs, mk); });
-    }
+    claimed_units<kNbufK>(
+        nku, kFirstK ? ln.wave : -1, [&]() __attribute__((always_inline)) { return claim(0); },
+        [&](auto slot, int u) __attribute__((always_inline)) { kp.load(krs, prs, u, kbuf[slot], pbuf[slot]); },
+        [&](auto slot, int u) __attribute__((always_inline)) { kp.logits(a, kbuf[slot], qv, pbuf[slot], u, nrows, zs, mk); });
 
     // the V stream's first loads are issued now, so their latency overlaps the K pass's epilogue (barriers
     // wait for LDS only, not for these loads)
@@ -348,11 +360,11 @@ void attend_kernel(ScoreArgs a) {
     if constexpr (kMV) {
 #pragma unroll
         for (int j = 0; j < kNbufV - 1; ++j) {
-            vnext[j] = claim(1);
+            vnext[j] = j == 0 ? ln.wave : claim(1);
             vu.load(vrs, vnext[j], vbufm[j]);
         }
     } else if constexpr (kV && kNbuf == 2) {
-        vfirst = claim(1);
+        vfirst = ln.wave;
         ln.load_rows(vrs, vfirst, vbuf[0]);
     }
 
