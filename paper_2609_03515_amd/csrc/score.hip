@@ -106,13 +106,14 @@ void score_lds_kernel(ScoreArgs a) {
         if (kVN && has_new) kp.load_row(static_cast<const T*>(a.v_new) + (size_t)sidx * D, vn);
     };
 
-    if (threadIdx.x < 2) next_unit[threadIdx.x] = 0;
+    // Vector form: the first units of the first slab go to the waves by index, and their loads wait for no claim and
+    // no barrier (one sequence of 32 layers x 8 KV heads x 3,278 tokens, one slab per CU: the step 44.0 -> 43.4 us,
+    // eight of them 263.2 -> 262.5).  The matrix-core form took the queries last so (7 heads, 8 x 25 x 4 slabs of 956
+    // rows 54.7 -> 55.0) and keeps its order.
+    constexpr bool kOwnFirst = !use_mfma<T, D, GP>();
+    if (threadIdx.x < 2) next_unit[threadIdx.x] = kOwnFirst && threadIdx.x == 0 ? (kNbuf - 1) * kWaves : 0;
     int sidx = slab_at(0);
     __amdgpu_buffer_rsrc_t krs = k_rsrc(sidx), prs = p_rsrc(sidx), nrs = n_rsrc(sidx);
-    typename KP::q_t qv;
-    typename KP::row_t kn;
-    load_slab_consts(sidx, qv, kn);
-    __syncthreads();
     auto claim = [&](int si) -> int {
         int u = 0;
         if (ln.lane == 0) u = atomicAdd(&next_unit[si & 1], 1);
@@ -137,7 +138,18 @@ void score_lds_kernel(ScoreArgs a) {
             load_unit(j);
         }
     };
-    prime(0);
+    if constexpr (kOwnFirst) {
+#pragma unroll
+        for (int j = 0; j < kNbuf - 1; ++j) {
+            ubuf[j] = j * kWaves + __builtin_amdgcn_readfirstlane(ln.wave);
+            load_unit(j);
+        }
+    }
+    typename KP::q_t qv;
+    typename KP::row_t kn;
+    load_slab_consts(sidx, qv, kn);
+    __syncthreads();
+    if constexpr (!kOwnFirst) prime(0);
     for (int si = 0; si < nslab; ++si) {
         const int gi = si % merge;  // position of the slab in its item
         typename KP::max_t mk = kp.max_init();
