@@ -9,10 +9,11 @@
 //   1. K pass: logits of the chunk's rows for the group's heads into LDS (the scorer's lane machinery and
 //      dynamic unit claiming), running per-head max;
 //   2. e = exp(z - max) in place with per-head sums (with the score: a pass of its own; without: by the wave
-//      that claims a block in the V pass), then the V pass: every lane accumulates e_h(row) * v(row) for the
-//      GP heads over its 16-byte V chunks, the probabilities of a row being GP consecutive LDS words;
-//   3. cross-lane / cross-wave reduction in a fixed order, then either the normalised output (one chunk per
-//      slab) or the chunk's unnormalised partial output with its per-head (max, sum);
+//      that claims a block in the V pass), then the V pass: on the matrix cores for bf16 rows of d = 128 and padded
+//      groups of 4 to 16 (VUnit); else every lane accumulates e_h(row) * v(row) for the GP heads over its 16-byte
+//      V chunks, the probabilities of a row being GP consecutive LDS words;
+//   3. cross-lane (vector form) and cross-wave reduction in a fixed order, then either the normalised output (one
+//      chunk per slab) or the chunk's unnormalised partial output with its per-head (max, sum);
 //   4. when the score is wanted: the group probability sums r of the rows (one chunk), or the chunk's
 //      exponentials (several chunks), which a combine kernel turns into outputs and scores.
 // Chunks exist so that one layer's slabs (batch x KV heads, e.g. 64) still occupy all 256 CUs.
@@ -276,8 +277,8 @@ struct VUnit {
 };
 
 // Waves per SIMD the compiler must leave room for: bf16 rows of d = 128 with groups of 4 (the 8B shape) are held
-// to 128 registers, i.e. two workgroups per CU, which the all-layer call (2,048 workgroups) uses: uncapped the
-// kernel takes 129 and that call with the score measured 1% slower.  Other instances keep what they need.
+// to 128 registers, i.e. two workgroups per CU, which the all-layer call (2,048 workgroups) uses (100 are taken; a
+// form that took 129 was 1% slower in that call).  Other instances keep what they need.
 template <typename T, int D, int GP, bool kV>
 constexpr int attend_waves_per_eu() {
     return (kV && GP == 4 && D == 128 && std::is_same<T, bf16_t>::value) ? 4 : 1;
@@ -575,12 +576,11 @@ void attend_kernel(ScoreArgs a) {
         if (ln.lane < GP) red_s[ln.wave][ln.lane] = ssum;  // read after the barriers below
     }
 
-    // 3. lanes holding the same chunk of different rows (stride LPR), then the waves in order.  With 16 lanes
-    //    per row the four rows hold the same chunks: four accumulators at a time are reduced over the rows with
+    // 3. vector form: lanes holding the same chunk of different rows (stride LPR), then the waves in order.  With 16
+    //    lanes per row the four rows hold the same chunks: four accumulators at a time are reduced over the rows with
     //    row swaps, leaving accumulator 4i + r in row r (in the butterfly's order, so the sums are unchanged),
-    //    and every lane stores its share of the wave's slice.  Measured at the 8B shape, one decoder layer per
-    //    call: 24.6 -> 23.4 us; the 64 cross-row shuffles of the butterfly had kept the LDS crossbar busy for
-    //    ~1 us after the V pass.
+    //    and every lane stores its share of the wave's slice (64 cross-row shuffles of a butterfly had kept the LDS
+    //    crossbar busy for ~1 us after the V pass).
     constexpr int kAcc = GP * CPL * EPC;
     constexpr bool kRowSwaps = kWaveSlices && LPR == 16 && kAcc % 4 == 0;
     if constexpr (!kRowSwaps && !kMV) {
