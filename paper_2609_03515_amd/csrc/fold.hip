@@ -18,8 +18,9 @@ namespace {
 constexpr int kQuads = 8;          // 4-token groups per workgroup (32 tokens)
 constexpr int kSlices = 32;        // layer slices per workgroup
 constexpr int kThreads = kQuads * kSlices;
-constexpr int kRows = 8;           // rows of r whose loads a thread keeps in flight
 
+// kRows: rows of r whose loads a thread keeps in flight (no more than a layer has: their registers cost occupancy).
+template <int kRows>
 __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
     __shared__ float partial[kSlices][kQuads * 4];
     __shared__ float partial_raw[kSlices][kQuads * 4];
@@ -138,7 +139,8 @@ int fold_groups(int n) { return (n + kQuads * 4 - 1) / (kQuads * 4); }
 
 hipError_t launch_fold(const FoldArgs& a, hipStream_t s) {
     dim3 grid(fold_groups(a.n), a.batch);
-    hipLaunchKernelGGL(fold_kernel, grid, dim3(kThreads), 0, s, a);
+    auto kern = a.r_groups <= 2 ? fold_kernel<2> : a.r_groups <= 4 ? fold_kernel<4> : fold_kernel<8>;
+    hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 
