@@ -741,9 +741,11 @@ void attend_kernel(ScoreArgs a) {
         return;
     }
 
-    // 4. one chunk: the score's group probability sums, staged in each unit's first RPW words (only this
-    //    wave reads its units, and the V pass is over) and written with 16-byte stores
+    // 4. one chunk: the score's group probability sums, staged in each unit's first RPW words (the V pass is over, so
+    //    only this wave reads its units, but for the non-finite outputs above, whose threads read every row's words)
+    //    and written with 16-byte stores
     if (a.emit && a.nchunk == 1) {
+        if constexpr (kMV) __syncthreads();
         static_assert(RPW % 4 == 0, "the coalesced store moves 4 rows at a time");
         const float tot = head_sum(ln.hh);
         const float inv = tot > 0.0f ? 1.0f / tot : 0.0f;

@@ -238,6 +238,57 @@ def test_attend_value_pass_edges(group, n):
     assert np.all(np.abs(got2 - got)[same] <= (4e-4 * scale + 2.0 ** -7 * np.abs(ref))[same])
 
 
+@pytest.mark.parametrize("emit", [0, 1])
+@pytest.mark.parametrize("group", [4, 7, 16])
+@pytest.mark.parametrize("n", [200, 700])
+def test_attend_infinite_value_weights(n, group, emit):
+    """An infinity among the values, with and without the score and with one chunk per slab and several, on a row whose
+    probability underflows to zero for the group's first head and for no other: 0 * inf is NaN for that head and an
+    infinity for the others, whatever is done with the probabilities afterwards (with one chunk, they are replaced by
+    the score's group sums).  Columns without an infinity, and the scores, are those of finite values."""
+    b, hkv, d = 2, 2, 128
+    hq = group * hkv
+    gen = torch.Generator(device="cpu").manual_seed(100 * n + 10 * group + emit)
+    k = torch.randn(1, b, hkv, n, d, generator=gen).clamp_(-4, 4).to(torch.bfloat16)
+    v = torch.randn(1, b, hkv, n, d, generator=gen).to(torch.bfloat16)
+    q = (0.5 * torch.randn(1, b, hq, d, generator=gen)).clamp_(-2, 2).to(torch.bfloat16)
+    rows = torch.arange(0, n, 3)
+    k[:, :, :, rows, 0] = 4.0      # logit 4 * -500 / sqrt(128) = -177 for the first heads
+    k[:, :, :, 1, 0] = 0.0         # (their maximum is no lower than this row's)
+    q[:, :, ::group, 0] = -500.0
+    pos = torch.arange(n, dtype=torch.int32).repeat(b, 1).contiguous()
+    shape = B.make_shape(b, 1, hq, hkv, d, n, "bf16")
+    ws = B.workspace(shape, n)
+    dk, dq, dpos = k.cuda(), q.cuda(), pos.cuda()
+
+    def attend(values):
+        o = torch.empty_like(dq)
+        u, s_out = torch.zeros(b, n, device="cuda"), torch.zeros(1, b, n, device="cuda")
+        dv = values.cuda()
+        B.kv_attend_score(shape, 0, 1, n, dq, dk, dv, dpos, n - 1, 0.0, 0, emit, o, ws)
+        if emit:
+            B.kv_evict_finish(shape, B.make_params(0.5, n), 1, n, dk, dv, u, dpos, ws, s_out=s_out)
+        torch.cuda.synchronize()
+        return to_f64(raw_numpy(o), "bf16"), s_out.cpu().numpy()
+
+    print(f"infinite value n={n} group={group} emit={emit}", flush=True)
+    finite, scores = attend(v)
+    odd = v.clone()
+    cols = torch.arange(0, d, 5)   # columns in every workgroup's waves, each with the infinity in a row of its own
+    for i, c in enumerate(cols.tolist()):
+        odd[0, :, :, rows[(7 * i) % len(rows)], c] = float("inf")
+    got, scores2 = attend(odd)
+    first = np.zeros(hq, dtype=bool)
+    first[::group] = True
+    assert np.all(np.isnan(got[:, :, first][..., cols])) and np.all(np.isposinf(got[:, :, ~first][..., cols]))
+    # the waves claim their rows, so two calls add in different orders: n * 2^-24 <= 4.2e-5 of the weighted values
+    # (at most the largest) on each side, and a step of bf16; of the scores on each side
+    rest = np.setdiff1d(np.arange(d), cols)
+    bound = 1e-4 * v.abs().max().item() + 2.0 ** -7 * np.abs(finite)
+    assert np.all(np.abs(got - finite)[..., rest] <= bound[..., rest])
+    np.testing.assert_allclose(scores2, scores, rtol=1e-4)
+
+
 @pytest.mark.parametrize("hq,hkv,n", [(1, 1, 4096), (16, 1, 4100), (7, 1, 4361), (1, 1, 8192), (3, 1, 16384),
                                       (16, 1, 90000), (3, 1, 331000)])
 def test_attend_chunk_counts(hq, hkv, n):
