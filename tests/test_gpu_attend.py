@@ -276,17 +276,62 @@ def test_attend_infinite_value_weights(n, group, emit):
     odd = v.clone()
     cols = torch.arange(0, d, 5)   # columns in every workgroup's waves, each with the infinity in a row of its own
     for i, c in enumerate(cols.tolist()):
-        odd[0, :, :, rows[(7 * i) % len(rows)], c] = float("inf")
+        odd[0, :, :, rows[(7 * i) % len(rows)], c] = float("inf") if i % 2 == 0 else float("-inf")
+    odd[0, :, :, 0, 3], odd[0, :, :, n - 1, 3] = float("inf"), float("-inf")  # both signs: NaN
+    odd[0, :, :, n // 2, 126] = float("nan")
     got, scores2 = attend(odd)
     first = np.zeros(hq, dtype=bool)
     first[::group] = True
-    assert np.all(np.isnan(got[:, :, first][..., cols])) and np.all(np.isposinf(got[:, :, ~first][..., cols]))
+    assert np.all(np.isnan(got[:, :, first][..., cols])) and np.all(np.isnan(got[..., [3, 126]]))
+    assert np.all(np.isposinf(got[:, :, ~first][..., cols[::2]])) and np.all(np.isneginf(got[:, :, ~first][..., cols[1::2]]))
     # the waves claim their rows, so two calls add in different orders: n * 2^-24 <= 4.2e-5 of the weighted values
     # (at most the largest) on each side, and a step of bf16; of the scores on each side
-    rest = np.setdiff1d(np.arange(d), cols)
+    rest = np.setdiff1d(np.arange(d), [3, 126, *cols.tolist()])
     bound = 1e-4 * v.abs().max().item() + 2.0 ** -7 * np.abs(finite)
     assert np.all(np.abs(got - finite)[..., rest] <= bound[..., rest])
     np.testing.assert_allclose(scores2, scores, rtol=1e-4)
+
+
+@pytest.mark.parametrize("what", ["query", "key", "values", "infinities"])
+@pytest.mark.parametrize("emit", [0, 1])
+def test_attend_nonfinite_inputs_are_not_slow(what, emit):
+    """One sequence with a NaN query, key or values, or an infinity in every value column, does not hold up the others'
+    call: at most twice the time of finite inputs (20 to 22 us a call; 32 with the infinities; 43 and more, in every case,
+    where each such output was summed again by its thread row by row), the least of several runs of each."""
+    b, hq, hkv, n, d = 8, 32, 8, 3278, 128
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    k, v = (torch.randn(1, b, hkv, n, d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(1, b, hq, d, generator=gen, device="cuda").to(torch.bfloat16)
+    pos = torch.arange(n, dtype=torch.int32, device="cuda").repeat(b, 1).contiguous()
+    shape = B.make_shape(b, 1, hq, hkv, d, n, "bf16")
+    ws = B.workspace(shape, n)
+    o = torch.empty_like(q)
+
+    def best():
+        times = []
+        for _ in range(8):
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            t0.record()
+            for _ in range(20):
+                B.kv_attend_score(shape, 0, 1, n, q, k, v, pos, n - 1, 0.0, 0, emit, o, ws)
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1) / 20)
+        return min(times)
+
+    print(f"non-finite {what} emit={emit}", flush=True)
+    clean = best()
+    if what == "query":
+        q[0, 0] = float("nan")
+    elif what == "key":
+        k[0, 0, :, 5] = float("nan")
+    elif what == "values":
+        v[0, 0] = float("nan")
+    else:
+        v[0, 0, :, torch.arange(d), torch.arange(d)] = float("inf")
+    got = best()
+    print(f"{clean * 1e3:.1f} us, non-finite {got * 1e3:.1f}", flush=True)
+    assert got <= 2.0 * clean
 
 
 @pytest.mark.parametrize("hq,hkv,n", [(1, 1, 4096), (16, 1, 4100), (7, 1, 4361), (1, 1, 8192), (3, 1, 16384),
