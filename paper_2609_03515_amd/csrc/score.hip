@@ -106,11 +106,13 @@ void score_lds_kernel(ScoreArgs a) {
         if (kVN && has_new) kp.load_row(static_cast<const T*>(a.v_new) + (size_t)sidx * D, vn);
     };
 
-    // Vector form: the first units of the first slab go to the waves by index, and their loads wait for no claim and
-    // no barrier (one sequence of 32 layers x 8 KV heads x 3,278 tokens, one slab per CU: the step 44.0 -> 43.4 us,
-    // eight of them 263.2 -> 262.5).  The matrix-core form took the queries last so (7 heads, 8 x 25 x 4 slabs of 956
-    // rows 54.7 -> 55.0) and keeps its order.
-    constexpr bool kOwnFirst = !use_mfma<T, D, GP>();
+    // Groups of 2 and 4: the first units of the first slab go to the waves by index, and their loads wait for no claim
+    // and no barrier.  Refresh steps, claimed and so: one sequence of 32 layers x 8 KV heads x 3,278 tokens (4 heads, one
+    // slab per CU) 44.1 and 43.6 us; f32 rows of 128, 2 x 16 x 8 slabs of 1,201, 2 heads 35.8 and 35.2, 4 heads 34.7 and
+    // 34.3.  Not with one head, where it gained nothing for bf16 (105.1 and 105.0) and its longer-lived buffers made the
+    // f32 instances spill (8 x 16 x 8 slabs 206 and 220, with VNorm 222 and 235), nor with more: larger queries then come
+    // last (8 heads in f32 26.15 and 26.56; matrix-core form, 7 heads, 54.7 and 55.0).
+    constexpr bool kOwnFirst = GP == 2 || GP == 4;
     if (threadIdx.x < 2) next_unit[threadIdx.x] = kOwnFirst && threadIdx.x == 0 ? (kNbuf - 1) * kWaves : 0;
     int sidx = slab_at(0);
     __amdgpu_buffer_rsrc_t krs = k_rsrc(sidx), prs = p_rsrc(sidx), nrs = n_rsrc(sidx);
