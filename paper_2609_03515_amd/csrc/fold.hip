@@ -19,7 +19,9 @@ constexpr int kQuads = 8;          // 4-token groups per workgroup (32 tokens)
 constexpr int kSlices = 32;        // layer slices per workgroup
 constexpr int kThreads = kQuads * kSlices;
 
-// kRows: rows of r whose loads a thread keeps in flight (no more than a layer has: their registers cost occupancy).
+// kRows: rows of r whose loads a thread keeps in flight (no more than a layer has: their registers cost occupancy); 0:
+// VNorm, whose rows are taken one by one (in the instance with eight rows in flight, 81 registers where it needs 47, the
+// finish of 32 sequences of 8 layers x 8 KV heads x 8,193 tokens took 57.3 us, in its own 50.1).
 template <int kRows>
 __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
     __shared__ float partial[kSlices][kQuads * 4];
@@ -43,9 +45,8 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
     if (tok0 < a.n) {
         for (int l = slice; l < a.layers; l += kSlices) {
             const float* rl = a.r + ((size_t)(l * a.batch + b) * a.r_groups) * a.n_stride + tok0;
-            f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f}, t = s;
-            int in_block = 0;
-            if (a.vnorm) {  // r_groups == hkv: one row per KV head
+            f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+            if constexpr (kRows == 0) {  // r_groups == hkv: one row per KV head
                 // VNorm: each KV head's group sum times the token's value-norm factor norm / mean norm
                 // (factor 1 where the slab's norms are all zero)
                 // norms in the workspace (stride n_stride, rows padded to 64: 16-byte loads) or in the caller's
@@ -74,6 +75,8 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(FoldArgs a) {
                 // block sums first, then the blocks in order; kRows rows' loads in flight (one at a time, eight
                 // rows per layer took eight latencies: the refresh step of one sequence of 32 layers x 8 KV heads x 3,278
                 // tokens 45.8 -> 44.0 us, the finish after its attention calls 8.3 -> 7.8)
+                f32x4 t = s;
+                int in_block = 0;
                 for (int g0 = 0; g0 < a.r_groups; g0 += kRows) {
                     f32x4 x[kRows];
 #pragma unroll
@@ -139,7 +142,10 @@ int fold_groups(int n) { return (n + kQuads * 4 - 1) / (kQuads * 4); }
 
 hipError_t launch_fold(const FoldArgs& a, hipStream_t s) {
     dim3 grid(fold_groups(a.n), a.batch);
-    auto kern = a.r_groups <= 2 ? fold_kernel<2> : a.r_groups <= 4 ? fold_kernel<4> : fold_kernel<8>;
+    auto kern = a.vnorm           ? fold_kernel<0>
+                : a.r_groups <= 2 ? fold_kernel<2>
+                : a.r_groups <= 4 ? fold_kernel<4>
+                                  : fold_kernel<8>;
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }

@@ -69,3 +69,10 @@ def test_scorer_spills(kernels):
     seen = {n[len("score_lds_kernel"):]: k[".vgpr_spill_count"] for n, k in kernels.items() if n.startswith("score_lds_kernel")}
     assert set(most) <= set(seen)
     assert {n: c for n, c in seen.items() if c > most.get(n, 0)} == {}
+
+
+def test_fold_registers(kernels):
+    """VNorm's fold, which keeps no rows in flight, is an instance of its own with 8 waves per SIMD (64 of 512
+    registers); so are the folds of few rows per layer."""
+    used = {i: kernels["fold_kernel" + i][".vgpr_count"] for i in ("<0>", "<2>", "<4>")}
+    assert max(used.values()) <= 64, used
