@@ -376,7 +376,9 @@ void attend_kernel(ScoreArgs a) {
     const __amdgpu_buffer_rsrc_t prs = raw_rsrc(a.pos + (size_t)b * a.cap + row0, nrows * 4);
 
     // the first unit of a wave is its own index, in both passes: its loads wait for no claim and no barrier (the same
-    // decode steps 812, 758 and 398 us with every unit claimed, 801, 744 and 387 so)
+    // decode steps 812, 758 and 398 us with every unit claimed, 801, 744 and 387 so).  Without the V pass the form of
+    // 8 f32 heads then takes 132 registers, one workgroup per CU: so 474 us for 8 slabs of 131,073 rows and 927 for 16,
+    // with every unit claimed and both counters set by one thread (128 registers, two workgroups) 482 and 946.
     constexpr bool kFirstK = kNbufK == 2;
     typename KP::max_t mk = kp.max_init();
     typename KP::buf_t kbuf[kNbufK];
