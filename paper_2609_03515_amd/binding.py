@@ -122,12 +122,17 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# torch's raw handle of a device's current stream, and the current device: internal names, None in a torch without them
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:
         # the current device's current stream.  Building torch's Stream object for it took 2.9 us of a call's 13
         # (one eviction step) or 10 (one layer's attention); the raw handle takes 0.2
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream is not None and _device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

@@ -327,3 +327,18 @@ def test_cache_wrapper_raises_and_keeps_n(lib):
     with pytest.raises(B.KVError):
         B.evict_step(cache, q, kv_new, kv_new, 1, params, new_pos=20, stream=0)
     assert cache.n == 16
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
+def test_stream_without_torchs_raw_handle(monkeypatch, missing):
+    """A torch without the internal handle: the public Stream object's is used."""
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 77)
+    monkeypatch.setattr(B, "_device", lambda: 0)
+    assert B._stream(None) == 77 and B._stream(5) == 5 and B._stream(Stream()) == 1234
+    monkeypatch.setattr(B, missing, None)
+    assert B._stream(None) == 1234

@@ -62,3 +62,13 @@ def test_graph_replay_matches_eager(cfg, period, steps):
             assert torch.equal(st[key][..., :n] if key in ("u", "pos") else st[key][..., :n, :],
                                ref[key][..., :n] if key in ("u", "pos") else ref[key][..., :n, :]), (rep, key)
         _ = (st["u"] * 2).sum().item()   # eager work between replays
+
+
+def test_calls_take_the_current_stream():
+    """Without a stream argument a call goes to torch's current stream: the default one, and a side stream's block."""
+    torch.zeros(1, device="cuda")
+    assert B._stream(None) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert B._stream(None) == side.cuda_stream
+    assert B._stream(None) == torch.cuda.current_stream().cuda_stream != side.cuda_stream
