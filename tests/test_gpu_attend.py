@@ -292,6 +292,38 @@ def test_attend_infinite_value_weights(n, group, emit):
     np.testing.assert_allclose(scores2, scores, rtol=1e-4)
 
 
+@pytest.mark.parametrize("emit", [0, 1])
+@pytest.mark.parametrize("L,b,hkv,group", [(1, 3, 4, 4), (1, 3, 3, 1), (3, 1, 5, 7), (2, 11, 1, 2)])
+def test_attend_slab_counts_beyond_eights(L, b, hkv, group, emit):
+    """Slabs are numbered in groups of eight, a group's chunks eight workgroups apart, and the last slabs in order: 12, 9,
+    15 and 22 slabs of several chunks, where both numberings meet in one launch of the attention and of its combine.
+    Bounds as in the geometries above; every slab has inputs of its own."""
+    d, n, hq = 128, 1100, hkv * group
+    gen = torch.Generator(device="cpu").manual_seed(100 * hkv + 10 * group + b)
+    k, v = (torch.randn(L, b, hkv, n, d, generator=gen).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(L, b, hq, d, generator=gen).to(torch.bfloat16)
+    pos = torch.arange(n, dtype=torch.int32).repeat(b, 1).contiguous()
+    shape = B.make_shape(b, L, hq, hkv, d, n, "bf16")
+    ws = B.workspace(shape, n)
+    dk, dv, dq, dpos = k.cuda(), v.cuda(), q.cuda(), pos.cuda()
+    o = torch.full_like(dq, float("nan"))
+    s_out = torch.full((L, b, n), float("nan"), device="cuda")
+    print(f"slabs L={L} b={b} hkv={hkv} group={group} emit={emit}", flush=True)
+    B.kv_attend_score(shape, 0, L, n, dq, dk, dv, dpos, n - 1, 0.0, 0, emit, o, ws)
+    if emit:
+        B.kv_evict_finish(shape, B.make_params(0.5, n), 1, n, dk, dv, torch.zeros(b, n, device="cuda"), dpos, ws,
+                          s_out=s_out)
+    torch.cuda.synchronize()
+    pr = np.arange(n)
+    for l in range(L):
+        for bb in range(b):
+            keys, ql = to_f64(raw_numpy(k)[l, bb], "bf16"), to_f64(raw_numpy(q)[l, bb], "bf16")
+            ref, scale = attention_output(ql, keys, to_f64(raw_numpy(v)[l, bb], "bf16"), pr, n - 1, 0.0, 0)
+            assert_o(o[l : l + 1, bb : bb + 1], ref[None, None], scale[None, None], "bf16", f"outputs of {l}, {bb}")
+            if emit:
+                assert_close(s_out[l, bb].cpu().numpy(), layer_scores(ql, keys, pr, n - 1, 0.0, 0), f"scores of {l}, {bb}")
+
+
 @pytest.mark.parametrize("what", ["query", "key", "values", "infinities"])
 @pytest.mark.parametrize("emit", [0, 1])
 def test_attend_nonfinite_inputs_are_not_slow(what, emit):
