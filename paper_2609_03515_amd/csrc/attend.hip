@@ -128,14 +128,14 @@ __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(ScoreAr
     }
 
     // one (head, chunk) pair per lane: a row of 16 lanes per head, or a wave; more chunks than that are taken from
-    // memory again where needed
+    // memory again where needed.  (A chunk with an infinite logit has no factor: w is NaN, and stays it.)
     if (nchunk <= 16) {
         const int h = tid / 16, c = tid % 16;
         if (h < group) {
             const float2 p = c < nchunk ? pp[h * nchunk + c] : make_float2(-INFINITY, 0.0f);
             const float w = __expf(p.x - row_allmax(p.x));
             const float tot = group_allsum<16>(w * p.y);
-            if (c < nchunk) fs[h * nchunk + c] = tot > 0.0f ? w / tot : 0.0f;
+            if (c < nchunk) fs[h * nchunk + c] = tot > 0.0f ? w / tot : w * 0.0f;
         }
     } else if (staged) {
         const int c = tid % kWave;
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kCombineThreads) void attend_combine_kernel(ScoreAr
             const float2 p = c < nchunk ? pp[h * nchunk + c] : make_float2(-INFINITY, 0.0f);
             const float w = __expf(p.x - wave_max(p.x));
             const float tot = wave_sum(w * p.y);
-            if (c < nchunk) fs[h * nchunk + c] = tot > 0.0f ? w / tot : 0.0f;
+            if (c < nchunk) fs[h * nchunk + c] = tot > 0.0f ? w / tot : w * 0.0f;
         }
     } else if (tid < group) {
         const float2* ph = pp + (size_t)tid * nchunk;

@@ -324,6 +324,31 @@ def test_attend_slab_counts_beyond_eights(L, b, hkv, group, emit):
                 assert_close(s_out[l, bb].cpu().numpy(), layer_scores(ql, keys, pr, n - 1, 0.0, 0), f"scores of {l}, {bb}")
 
 
+@pytest.mark.parametrize("hq,hkv,n", [(4, 1, 700), (4, 1, 6000), (4, 1, 20000), (16, 1, 90000)])
+def test_attend_infinite_logit(hq, hkv, n):
+    """An infinite logit makes its head's softmax undefined: the outputs are NaN, and so are the scores of the rows that
+    share its chunk, however many chunks there are (3, 24, 64 and 71 here: the combine takes up to 16, up to 64 and more
+    in different ways), not an ordinary score of zero."""
+    d, row = 128, n // 2
+    gen = torch.Generator(device="cpu").manual_seed(n)
+    k, v = (torch.randn(1, 1, hkv, n, d, generator=gen).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(1, 1, hq, d, generator=gen).to(torch.bfloat16)
+    k[..., row, 0] = float("inf")
+    q[0, 0, :, 0] = -1.0
+    q[0, 0, 1, 0] = 1.0        # of the heads, one takes +inf, the others -inf (a probability of zero)
+    pos = torch.arange(n, dtype=torch.int32).repeat(1, 1).contiguous()
+    shape = B.make_shape(1, 1, hq, hkv, d, n, "bf16")
+    ws = B.workspace(shape, n)
+    dk, dv, dq, dpos = k.cuda(), v.cuda(), q.cuda(), pos.cuda()
+    o, u, s_out = torch.empty_like(dq), torch.zeros(1, n, device="cuda"), torch.zeros(1, 1, n, device="cuda")
+    print(f"infinite logit hq={hq} n={n}", flush=True)
+    B.kv_attend_score(shape, 0, 1, n, dq, dk, dv, dpos, n - 1, 0.0, 0, B.KV_EMIT_SCORES, o, ws)
+    B.kv_evict_finish(shape, B.make_params(0.5, n), 1, n, dk, dv, u, dpos, ws, s_out=s_out)
+    torch.cuda.synchronize()
+    assert torch.isnan(o[0, 0, 1]).all() and torch.isfinite(o[0, 0, 0].float()).all()
+    assert torch.isnan(s_out[0, 0, row - 4 : row + 5]).all()
+
+
 @pytest.mark.parametrize("what", ["query", "key", "values", "infinities"])
 @pytest.mark.parametrize("emit", [0, 1])
 def test_attend_nonfinite_inputs_are_not_slow(what, emit):
