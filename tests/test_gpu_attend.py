@@ -395,8 +395,8 @@ def test_attend_nonfinite_inputs_are_not_slow(what, emit):
                                       (16, 1, 90000), (3, 1, 331000)])
 def test_attend_chunk_counts(hq, hkv, n):
     """The combine's ways of taking the chunks' statistics: up to 16 chunks per slab (16, 17 and 18 here), up to 64
-    (32 and 64) and more (71 and 65: the LDS of one chunk holds 1,280 or 5,120 rows).  Bounds as in the geometries
-    above (the oracle's own tolerance)."""
+    (32 and 64) and more (256, twice: one per CU for a single slab).  Bounds as in the geometries above (the oracle's own
+    tolerance)."""
     d = 128
     gen = torch.Generator(device="cpu").manual_seed(n)
     k = torch.randn(1, 1, hkv, n, d, generator=gen).to(torch.bfloat16)
