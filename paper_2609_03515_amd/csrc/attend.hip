@@ -326,7 +326,7 @@ __device__ float nonfinite_column(__amdgpu_buffer_rsrc_t vrs, int col0, int nrow
 }
 
 // Waves per SIMD the compiler must leave room for: bf16 rows of d = 128 with groups of 4 (the 8B shape) are held
-// to 128 registers, i.e. two workgroups per CU, which the all-layer call (2,048 workgroups) uses (100 are taken; a
+// to 128 registers, i.e. two workgroups per CU, which the all-layer call (2,048 workgroups) uses (99 are taken; a
 // form that took 129 was 1% slower in that call).  Other instances keep what they need.
 template <typename T, int D, int GP, bool kV>
 constexpr int attend_waves_per_eu() {
@@ -353,7 +353,11 @@ void attend_kernel(ScoreArgs a) {
     constexpr bool kMV = kV && use_mfma_v<T, D, GP>();
     constexpr bool kFirstV = kV && (kMV || kNbuf == 2);
     constexpr bool kWaveSlices = kWaves * GP * D <= 4096 && !kMV;
-    constexpr int kMVSlices = GP > 8 ? kWaves / 2 : kWaves;  // matrix-core form: at most 32 KiB of slices
+    // matrix-core form: at most 32 KiB of slices.  Beside more than 47 KiB of logits they leave a CU one workgroup, which
+    // is enough: one call over 28 layers x 32 sequences x 4 KV heads (7 heads) streams K and V at 6.9 TB/s with 2,049 rows
+    // (64 KiB of logits, one workgroup: 546 us, 587 with the score) and at 6.7 with 1,100 (35 KiB, two: 302 and 321).  The
+    // vector form (190 registers, one workgroup) took 1,022, 1,045, 782 and 804.
+    constexpr int kMVSlices = GP > 8 ? kWaves / 2 : kWaves;
     extern __shared__ float zs[];
     __shared__ float red_m[kWaves][GP], red_s[kWaves][GP], red_n[kWaves];
     __shared__ float obuf[kV ? (kMV ? kMVSlices : kWaveSlices ? kWaves : 1) * GP * D : 1];

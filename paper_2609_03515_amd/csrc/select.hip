@@ -642,8 +642,8 @@ __global__ __launch_bounds__(kWideThreads) void wide_count_kernel(SelectArgs a, 
     }
 }
 
-// Pairs: wave j of a slice takes its j-th quarter (whole 64-slot groups) and writes its holes and tails at the
-// ranks after the earlier slices and quarters; the last slice records the pair count.
+// Pairs: wave j of a slice takes its j-th eighth (whole 64-slot groups) and writes its holes and tails at the
+// ranks after the earlier slices and eighths; the last slice records the pair count.
 __global__ __launch_bounds__(kWideThreads) void wide_plan_kernel(SelectArgs a, Wide w) {
     constexpr int kW = kWideThreads / kWave;
     __shared__ unsigned base[2], wc[kW][2];

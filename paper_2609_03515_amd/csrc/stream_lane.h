@@ -27,7 +27,9 @@ namespace {
 #define IKV_LPR 16
 #endif
 
-constexpr size_t kFastLdsMax = 80 * 1024;  // keep >= 2 workgroups per CU (160 KiB LDS)
+// The most logits of a workgroup: two workgroups per CU (160 KiB of LDS) up to 79 KiB beside the scorers' few static
+// words.  (The attention's value pass adds its waves' slices, up to 32 KiB: two per CU up to 47 KiB of logits, else one.)
+constexpr size_t kFastLdsMax = 80 * 1024;
 constexpr int kWaves = IKV_SCORE_WAVES;
 constexpr int kThreads = kWaves * kWave;
 constexpr float kFloor = -1.0e30f;  // finite start of running maxima: exp(-inf - floor) = 0, no NaN
